@@ -58,6 +58,17 @@ __device__ inline U4 philox4x32_10_uk(U4 c, uint32_t k0, uint32_t k1)
     return philox4x32_10(c, k0, k1);
 }
 
+// -ln(w) for w in (0, 1] that is a multiple of 2^-24: the steps of __logf with
+// the ones for subnormal, infinite and NaN arguments left out (the same value
+// for all 2^24 arguments, up to the sign of -ln(1) = 0).
+__device__ inline float neg_log_unit(float w)
+{
+    const float y = -__builtin_amdgcn_logf(w);   // (log2)
+    const float p = y * 0x1.62e42ep-1f;
+    const float e = __builtin_fmaf(y, 0x1.62e42ep-1f, -p);
+    return p + __builtin_fmaf(y, 0x1.efa39ep-25f, e);
+}
+
 // A path's random stream: counter = (a, b, draw, stream), key = seed.  Each
 // Philox call yields four uniforms, consumed in order.
 struct Rng {
@@ -91,7 +102,7 @@ struct Rng {
         return (float)(v >> 8) * 5.9604644775390625e-08f;
     }
     // optical thickness ~ Exp(1)
-    __device__ float exp1() { return -__logf(1.0f - u01()); }
+    __device__ float exp1() { return neg_log_unit(1.0f - u01()); }
 
     // Batched draws: need(k) makes sure k uniforms are buffered (a fresh
     // Philox block replaces a buffer holding fewer), take() consumes one
@@ -113,7 +124,7 @@ struct Rng {
         --left;
         return (float)(v >> 8) * 5.9604644775390625e-08f;
     }
-    __device__ float take_exp1() { return -__logf(1.0f - take()); }
+    __device__ float take_exp1() { return neg_log_unit(1.0f - take()); }
 };
 
 // The same stream with its counter words supplied by the caller at each
@@ -145,7 +156,7 @@ struct RngBuf {
         --left;
         return (float)(v >> 8) * 5.9604644775390625e-08f;
     }
-    __device__ float take_exp1() { return -__logf(1.0f - take()); }
+    __device__ float take_exp1() { return neg_log_unit(1.0f - take()); }
 };
 
 // ---------------------------------------------------------------------------
@@ -167,6 +178,10 @@ struct GridView {
     const float2 *nodes;
     const int *off;      // device array: node offset of level l at index l, off[L+1] = total
     const uint16_t *mask;  // per level-1 node [z][y][x]: bit l (1..L) set if the level-l ancestor is merged
+    // nx ny < 2^24 and fewer than 2^30 cells: element numbers by full-rate
+    // 24-bit multiply-adds and byte offsets in 32 bits (the general form takes
+    // quarter-rate 32-bit products and 64-bit address adds)
+    int narrow = 0;
 };
 
 __host__ __device__ inline int level_dim(int n, int l) { return (n + (1 << l) - 1) >> l; }
@@ -185,7 +200,32 @@ struct NodeSrc {
     int lds_first;
     int lds_base;        // off[lds_first]
     int n0, n1;
+    const int4 *rows = nullptr;   // per level (LDS): node offset (within the staged block for a staged level),
+                                  // nodes per row, nodes per slice, 0
 };
+
+// a b + c for a, b < 2^24 (one full-rate instruction on the GPU)
+__host__ __device__ inline uint32_t mad24(uint32_t a, uint32_t b, uint32_t c)
+{
+    return (a & 0xffffffu) * (b & 0xffffffu) + c;
+}
+
+// (int)floorf(x) in one instruction (finite x; saturates like the conversion)
+__host__ __device__ inline int floor_int(float x)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    int j;
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(j) : "v"(x));
+    return j;
+#else
+    return (int)floorf(x);
+#endif
+}
+
+__host__ __device__ inline int clamp_int(int j, int lo, int hi)   // lo <= hi
+{
+    return j < lo ? lo : (j > hi ? hi : j);
+}
 
 __host__ __device__ inline float2 fetch_node(const NodeSrc &s, int l, int c0, int c1, int c2, uint32_t &gcount)
 {
@@ -207,12 +247,14 @@ __host__ __device__ inline float2 fetch_node(const NodeSrc &s, int l, int c0, in
 // floor of the position, clamped).  Only the voxel matters to the walk, the
 // exit axes always move forward and no axis steps back across a voxel face,
 // so the walk visits each voxel at most once and ends after at most
-// nx + ny + nz voxels.
+// nx + ny + nz voxels.  The cell past the exit face is found together with
+// the exit parameter (both need the voxel's two faces per axis): the crossing
+// itself is then a copy.
 //
 // The crossing functions are compiled for the host as well (a bit-exact
 // FP32 twin for testing the walk on every ray): they use only IEEE
-// operations that round the same on both sides (no approximate reciprocal;
-// the library is built without FP contraction).
+// operations that round the same on both sides (the GPU's short reciprocal is
+// correctly rounded; the library is built without FP contraction).
 // ---------------------------------------------------------------------------
 struct Ray {
     float o[3], d[3], inv[3];
@@ -222,8 +264,39 @@ struct Ray {
     float khat;          // voxel majorant m (kscale kmax_c + k_gas)
     float kmin;          // voxel minimum of k_c (for a level-0 voxel: k_c of the cell)
     float texit;         // voxel exit parameter
+    int cn[3];           // first cell past the exit face (set with texit)
     int xmask;           // axes whose voxel face is met at texit (bit a)
 };
+
+// 1 / d rounded to nearest, NaN for d = 0.  v_rcp_f32 and one Newton step in
+// FMAs give the correctly rounded reciprocal of every normal |d| < 2^126
+// (checked over all mantissas and exponents) in 3 instructions where the IEEE
+// division takes 10; other d (the caller's `odd`) take the division.
+__host__ __device__ inline float ray_inv(float d, bool odd)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    const float y = __builtin_amdgcn_rcpf(d);
+    float q = __builtin_fmaf(__builtin_fmaf(-d, y, 1.0f), y, y);
+    if (odd) q = d == 0.0f ? __builtin_nanf("") : 1.0f / d;
+    return q;
+#else
+    (void)odd;
+    return d == 0.0f ? __builtin_nanf("") : 1.0f / d;
+#endif
+}
+
+// a direction with a subnormal component or one of 2^126 or more
+__host__ __device__ inline bool ray_odd(const float d[3])
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    const float m = fmaxf(fmaxf(fabsf(d[0]), fabsf(d[1])), fabsf(d[2]));
+    return __builtin_amdgcn_classf(d[0], 0x90) | __builtin_amdgcn_classf(d[1], 0x90) |
+           __builtin_amdgcn_classf(d[2], 0x90) | (m >= 0x1p126f);
+#else
+    (void)d;
+    return false;
+#endif
+}
 
 __host__ __device__ inline float face_t(const GridView &g, const Ray &r, int a, int j)
 {
@@ -231,30 +304,31 @@ __host__ __device__ inline float face_t(const GridView &g, const Ray &r, int a, 
 }
 
 // Clip o + t d (t >= tmin) to the box; false if it misses.
+// An axis the ray is parallel to (d = 0) has inv = NaN: its face parameters
+// are NaN, which min, max and the comparisons below pass over.
 __host__ __device__ inline bool ray_setup(const GridView &g, Ray &r, const float o[3], const float d[3], float tmin)
 {
     float tin = tmin, tout = INFINITY;
     bool miss = false;
-    float tlo[3], thi[3];
+    float tlo[3];
+    const bool odd = ray_odd(d);
     // per axis, as selects (lanes that disagree would run both sides of a branch)
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         r.o[a] = o[a];
         r.d[a] = d[a];
-        const bool flat = d[a] == 0.0f;   // parallel to the axis' faces: inside their slab or a miss
-        r.inv[a] = flat ? INFINITY : 1.0f / d[a];   // correctly rounded (the host twin divides alike)
+        r.inv[a] = ray_inv(d[a], odd);
         // (both faces straight from the grid view, not through face_t: the
         // compiler cannot fold 0 h, and the hoisted per-axis values held through a
         // persistent loop cost registers)
         const float b0 = g.lo[a], b1 = g.hi[a];
-        miss = miss || (flat && (o[a] < b0 || o[a] > b1));
+        miss |= (d[a] == 0.0f) & ((o[a] < b0) | (o[a] > b1));   // parallel to the axis' faces and outside their slab
         const float t0 = (b0 - r.o[a]) * r.inv[a], t1 = (b1 - r.o[a]) * r.inv[a];
         tlo[a] = t0 > t1 ? t1 : t0;
-        thi[a] = t0 > t1 ? t0 : t1;
-        tin = flat ? tin : fmaxf(tin, tlo[a]);
-        tout = flat ? tout : fminf(tout, thi[a]);
+        tin = fmaxf(tin, tlo[a]);
+        tout = fminf(tout, t0 > t1 ? t0 : t1);
     }
-    if (miss || !(tin < tout)) return false;
+    if (miss | !(tin < tout)) return false;
     r.t = tin;
     r.tend = tout;
     // starting cell: exact on the axis through whose face the ray enters the
@@ -262,12 +336,9 @@ __host__ __device__ inline bool ray_setup(const GridView &g, Ray &r, const float
     // matters for the walk, and the walk never steps back across a face
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        int j = (int)floorf((o[a] + tin * d[a] - g.lo[a]) * g.inv_h[a]);
-        j = j < 0 ? 0 : (j > g.n[a] - 1 ? g.n[a] - 1 : j);
-        const bool entered = tin > tmin && tlo[a] == tin;   // entered through this axis' face
-        j = (entered && d[a] > 0.0f) ? 0 : j;
-        j = (entered && d[a] < 0.0f) ? g.n[a] - 1 : j;
-        r.c[a] = j;
+        const int j = clamp_int(floor_int((o[a] + tin * d[a] - g.lo[a]) * g.inv_h[a]), 0, g.n[a] - 1);
+        const bool entered = (tin > tmin) & (tlo[a] == tin);   // entered through this axis' face
+        r.c[a] = entered ? (d[a] > 0.0f ? 0 : g.n[a] - 1) : j;
     }
     return true;
 }
@@ -280,32 +351,64 @@ __host__ __device__ inline void leaf_exit(const GridView &g, Ray &r);
 // bit); the cell's own value is read at the same time, so a level-0 voxel
 // costs one round trip to memory and a coarser one at most two (none when
 // its level is staged in LDS).
+// kUnit: the grid view's kscale is 1.
+template <bool kUnit = false>
 __host__ __device__ inline void locate_voxel(const GridView &g, const NodeSrc &ns, Ray &r, float mscale,
                                              uint32_t &node_reads)
 {
     float kmin, kmax;
     int l = 0;
     // cell indices are >= 0; the row index fits 32 bits (n1, n2 <= 2^15)
-    const uint32_t row = (uint32_t)r.c[2] * (uint32_t)g.n[1] + (uint32_t)r.c[1];
-    const uint64_t cell = (uint64_t)row * (uint32_t)g.n[0] + (uint32_t)r.c[0];
-    const float kcell = g.kc[cell];
-    ++node_reads;
-    if (g.L >= 1) {
-        const int d0 = level_dim(g.n[0], 1), d1 = level_dim(g.n[1], 1);
-        const uint32_t mrow = (uint32_t)(r.c[2] >> 1) * (uint32_t)d1 + (uint32_t)(r.c[1] >> 1);
-        const uint32_t m = g.mask[(uint64_t)mrow * (uint32_t)d0 + (uint32_t)(r.c[0] >> 1)];
-        ++node_reads;
-        l = m ? 31 - __builtin_clz(m) : 0;
-    }
-    if (l == 0) {
+    if (g.narrow && ns.rows) {
+        const uint32_t x = (uint32_t)r.c[0], y = (uint32_t)r.c[1], z = (uint32_t)r.c[2];
+        const uint32_t cell = mad24(z, (uint32_t)(g.n[0] * g.n[1]), mad24(y, (uint32_t)g.n[0], x));
+        const float kcell = *(const float *)((const char *)g.kc + (cell << 2));
+        const uint32_t d0 = (uint32_t)level_dim(g.n[0], 1), d1 = (uint32_t)level_dim(g.n[1], 1);
+        const uint32_t mi = mad24(z >> 1, d0 * d1, mad24(y >> 1, d0, x >> 1));
+        const uint32_t m = *(const uint16_t *)((const char *)g.mask + (mi << 1));   // (L >= 1: a narrow grid has a mask)
+        node_reads += 2;
+        l = 31 - __builtin_clz(m | 1u);
         kmin = kmax = kcell;
+        if (l != 0) {
+            const int4 row = ns.rows[l];
+            const uint32_t idx = mad24(z >> l, (uint32_t)row.z, mad24(y >> l, (uint32_t)row.y, (x >> l) + (uint32_t)row.x));
+            float2 nd;
+            // two loads on two paths (not one flat load through a selected
+            // address, which waits for both memories)
+            if (l >= ns.lds_first) {
+                nd = ns.lds[idx];
+#ifdef __HIP_DEVICE_COMPILE__
+                asm volatile("" : "+v"(nd.x), "+v"(nd.y));
+#endif
+            } else {
+                ++node_reads;
+                nd = *(const float2 *)((const char *)ns.glob + (idx << 3));
+            }
+            kmin = node_kmin(nd);
+            kmax = nd.y;
+        }
     } else {
-        const float2 nd = fetch_node(ns, l, r.c[0], r.c[1], r.c[2], node_reads);
-        kmin = node_kmin(nd);
-        kmax = nd.y;
+        const uint32_t row = (uint32_t)r.c[2] * (uint32_t)g.n[1] + (uint32_t)r.c[1];
+        const uint64_t cell = (uint64_t)row * (uint32_t)g.n[0] + (uint32_t)r.c[0];
+        const float kcell = g.kc[cell];
+        ++node_reads;
+        if (g.L >= 1) {
+            const int d0 = level_dim(g.n[0], 1), d1 = level_dim(g.n[1], 1);
+            const uint32_t mrow = (uint32_t)(r.c[2] >> 1) * (uint32_t)d1 + (uint32_t)(r.c[1] >> 1);
+            const uint32_t m = g.mask[(uint64_t)mrow * (uint32_t)d0 + (uint32_t)(r.c[0] >> 1)];
+            ++node_reads;
+            l = m ? 31 - __builtin_clz(m) : 0;
+        }
+        if (l == 0) {
+            kmin = kmax = kcell;
+        } else {
+            const float2 nd = fetch_node(ns, l, r.c[0], r.c[1], r.c[2], node_reads);
+            kmin = node_kmin(nd);
+            kmax = nd.y;
+        }
     }
     r.lev = l;
-    r.khat = mscale * (g.kscale * kmax + g.k_gas);
+    r.khat = mscale * ((kUnit ? kmax : g.kscale * kmax) + g.k_gas);
     r.kmin = kmin;
 }
 
@@ -316,27 +419,31 @@ __host__ __device__ inline void find_leaf(const GridView &g, const NodeSrc &ns, 
     leaf_exit(g, r);
 }
 
-// Exit parameter of the current voxel (its faces clipped to the field).
+// Exit parameter of the current voxel (its faces clipped to the field) and
+// the first cell past the exit face.  A face on the box's side needs no
+// exception: its parameter is the one tend was taken from, bit for bit, or
+// beyond it, and at tend the ray ends without using the next cell.
 __host__ __device__ inline void leaf_exit(const GridView &g, Ray &r)
 {
     const int l = r.lev;
-    float te = r.tend;
     float tf[3];
-    // per axis: the face the ray leaves the voxel through, if it lies inside
-    // the field (the box faces are tend); selects, not branches: lanes that
-    // disagree would run both sides anyway
+    int lo[3], hi[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const int i = r.c[a] >> l;
-        const bool pos = r.d[a] > 0.0f;
-        const int j = pos ? min((i + 1) << l, g.n[a]) : (i << l);
-        const bool inner = pos ? j < g.n[a] : ((r.d[a] < 0.0f) & (j > 0));
-        const float t = face_t(g, r, a, j);
-        tf[a] = inner ? t : INFINITY;
-        te = fminf(te, tf[a]);
+        lo[a] = (r.c[a] >> l) << l;
+        hi[a] = min(lo[a] + (1 << l), g.n[a]);
+        tf[a] = face_t(g, r, a, r.d[a] > 0.0f ? hi[a] : lo[a]);
     }
+    float te = fminf(fminf(fminf(r.tend, tf[0]), tf[1]), tf[2]);
+    const float tx = te < r.t ? r.t : te;
     r.xmask = (tf[0] == te ? 1 : 0) | (tf[1] == te ? 2 : 0) | (tf[2] == te ? 4 : 0);
-    r.texit = te < r.t ? r.t : te;
+    r.texit = tx;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        // the exit axes step across their face, the others stay inside the voxel's slab
+        const int j = clamp_int(floor_int((r.o[a] + tx * r.d[a] - g.lo[a]) * g.inv_h[a]), lo[a], hi[a] - 1);
+        r.cn[a] = tf[a] == te ? (r.d[a] > 0.0f ? hi[a] : lo[a] - 1) : j;
+    }
 }
 
 // Cross the current voxel's exit face: the ray moves to its exit parameter
@@ -344,19 +451,11 @@ __host__ __device__ inline void leaf_exit(const GridView &g, Ray &r)
 // box).  The voxel there is not located.
 __host__ __device__ inline bool step_cell(const GridView &g, Ray &r)
 {
+    (void)g;
     r.t = r.texit;
     if (!(r.t < r.tend)) return false;
-    const int l = r.lev;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const int vlo = (r.c[a] >> l) << l;
-        const int vhi = min(vlo + (1 << l), g.n[a]) - 1;
-        const int across = r.d[a] > 0.0f ? vhi + 1 : vlo - 1;    // across the exit face
-        int j = (int)floorf((r.o[a] + r.t * r.d[a] - g.lo[a]) * g.inv_h[a]);
-        j = j < vlo ? vlo : (j > vhi ? vhi : j);                  // still inside the voxel's slab
-        const int nc = (r.xmask & (1 << a)) ? across : j;
-        r.c[a] = r.d[a] == 0.0f ? r.c[a] : nc;
-    }
+    for (int a = 0; a < 3; ++a) r.c[a] = r.cn[a];
     return true;
 }
 
@@ -370,7 +469,10 @@ __host__ __device__ inline bool next_leaf(const GridView &g, const NodeSrc &ns, 
 }
 
 // Cell holding the point at parameter t, kept inside the current voxel so
-// that the gathered k never exceeds the voxel's majorant.
+// that the gathered k never exceeds the voxel's majorant.  The voxel is found
+// from the next cell (which lies in its slab on every axis but those of the
+// exit face, one cell past it there), so that no register holds the current
+// cell between the crossing and a collision.
 __device__ inline size_t collision_cell(const GridView &g, const Ray &r, float t)
 {
     const int l = r.lev;
@@ -378,10 +480,10 @@ __device__ inline size_t collision_cell(const GridView &g, const Ray &r, float t
     // (a level-0 voxel clamps to its own cell)
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const int base = (r.c[a] >> l) << l;
+        const int past = (r.xmask & (1 << a)) ? (r.d[a] > 0.0f ? 1 : -1) : 0;
+        const int base = ((r.cn[a] - past) >> l) << l;
         const int top = min(base + (1 << l), g.n[a]) - 1;
-        int j = (int)floorf((r.o[a] + t * r.d[a] - g.lo[a]) * g.inv_h[a]);
-        cc[a] = j < base ? base : (j > top ? top : j);
+        cc[a] = clamp_int(floor_int((r.o[a] + t * r.d[a] - g.lo[a]) * g.inv_h[a]), base, top);
     }
     const uint32_t row = (uint32_t)cc[2] * (uint32_t)g.n[1] + (uint32_t)cc[1];
     return (size_t)((uint64_t)row * (uint32_t)g.n[0] + (uint32_t)cc[0]);
@@ -671,9 +773,19 @@ __device__ inline void start_ray_cached(const GridView &g, const NodeSrc &ns, Ra
     }
 }
 
-__device__ inline void stage_levels(const GridView &g, int lds_first, int lds_nodes, float2 *s_nodes, int *s_off)
+// The level offsets and the staged levels' nodes into LDS; rows (may be
+// null): the level table of locate_voxel.  Ends with a block barrier.
+__device__ inline void stage_levels(const GridView &g, int lds_first, int lds_nodes, float2 *s_nodes, int *s_off,
+                                    int4 *rows = nullptr)
 {
-    for (int i = threadIdx.x; i < NC_MAX_LEVELS + 2; i += blockDim.x) s_off[i] = i <= g.L + 1 ? g.off[i] : 0;
+    for (int i = threadIdx.x; i < NC_MAX_LEVELS + 2; i += blockDim.x) {
+        s_off[i] = i <= g.L + 1 ? g.off[i] : 0;
+        if (rows) {
+            const int d0 = level_dim(g.n[0], min(i, 30)), d1 = level_dim(g.n[1], min(i, 30));
+            const int base = i >= lds_first && i <= g.L ? g.off[lds_first] : 0;
+            rows[i] = make_int4(i <= g.L ? g.off[i] - base : 0, d0, d0 * d1, 0);
+        }
+    }
     if (lds_nodes > 0) {
         const int base = g.off[lds_first];
         for (int i = threadIdx.x; i < lds_nodes; i += blockDim.x) s_nodes[i] = g.nodes[base + i];

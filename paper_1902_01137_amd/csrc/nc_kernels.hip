@@ -1210,6 +1210,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
     static_assert(!kSets || kMode == kGuided, "queue sets are for guided batches");
     extern __shared__ __align__(16) float2 s_nodes[];
     __shared__ int s_off[NC_MAX_LEVELS + 2];
+    __shared__ int4 s_rows[NC_MAX_LEVELS + 2];
     __shared__ unsigned long long s_cnt[kNumBlockCounters];
     __shared__ int s_next_set;
     __shared__ RareShared s_rare;
@@ -1229,10 +1230,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
             stage_guide(W, reinterpret_cast<short *>(gb), reinterpret_cast<float *>(gb + kWOff[4] * 2));
         }
     }
-    stage_levels(A.g, A.lds_first, A.lds_nodes, s_nodes, s_off);   // ends with a block barrier
+    stage_levels(A.g, A.lds_first, A.lds_nodes, s_nodes, s_off, s_rows);   // ends with a block barrier
     const GridView &g = A.g;
     const NodeSrc ns{g.nodes, s_nodes, s_off, A.lds_first, s_off[A.lds_first <= g.L ? A.lds_first : 0], g.n[0],
-                     g.n[1]};
+                     g.n[1], s_rows};
     // launch-record fields, read from LDS at each use
 #define NC_R(f) lds_get(s_rare.f)
     const int lane = __lane_id();
@@ -1283,15 +1284,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
 #define NC_SET_QUEUE() (NC_R(queue) + 128 * cur)
     for (;;) {   // one queue set at a time (a single pass unless guides differ across jobs)
     for (;;) {
-        // lane counts per phase (scalar: 32-bit popcounts of the ballots); a
-        // crossing step and a ray start run in the same trip (the step phase)
-        const int n_step = (int)__builtin_amdgcn_readfirstlane(
-            __popcll(__ballot((phase == kPhCross) | (phase == kPhRay))));
-        const int n_coll = (int)__builtin_amdgcn_readfirstlane(__popcll(__ballot(phase == kPhCollide)));
-        const int n_event = (int)__builtin_amdgcn_readfirstlane(__popcll(__ballot(phase == kPhEvent)));
-        const int n_sample = (int)__builtin_amdgcn_readfirstlane(__popcll(__ballot(phase == kPhSample)));
-        const int n_guide =
-            kMode == kGuided ? (int)__builtin_amdgcn_readfirstlane(__popcll(__ballot(phase == kPhGuide))) : 0;
+        // lane counts per phase (scalar); a crossing step and the first voxel of
+        // a new ray run in the same trip (the step phase)
+        const int n_step = __builtin_popcountll(__ballot((phase == kPhCross) | (phase == kPhRay)));
+        const int n_coll = __builtin_popcountll(__ballot(phase == kPhCollide));
+        const int n_event = __builtin_popcountll(__ballot(phase == kPhEvent));
+        const int n_sample = __builtin_popcountll(__ballot(phase == kPhSample));
+        const int n_guide = kMode == kGuided ? __builtin_popcountll(__ballot(phase == kPhGuide)) : 0;
         const int n_other = n_step + n_coll + n_event + n_sample;
         if (n_other + n_guide == 0) break;
         int run = kPhCross, best = n_step;
@@ -1318,72 +1317,44 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
             atomicAdd(s_cnt + kCLanes0 + run, (unsigned long long)best);
         }
         const long long t_trip = stats ? wall_clock64() : 0;
+        bool start = false;   // the lane starts a ray at the end of this trip (along pd, or towards the sun)
 
         if (run == kPhCross) {
             // ---- a step of the ordered crossing: lanes crossing into the next
-            // voxel (carrying the optical thickness) and lanes starting a ray
-            // (from an event point along pd or towards the sun, or from the
-            // camera) share the location of the voxel (ancestry mask, node)
-            // and its exit face
-            const bool crossing = phase == kPhCross, starting = phase == kPhRay;
+            // voxel (carrying the optical thickness) and lanes in the first
+            // cell of a new ray share the location of the voxel (ancestry mask,
+            // node) and its exit
+            const bool crossing = phase == kPhCross;
             const bool resid = crossing && shadow && kSun == 2;
-            bool locate = false, leaf = false, hit = false, trunc = false;
-            if (resid) t_sun *= __expf(-(g.kscale * r.kmin + path_kg()) * (r.texit - r.t));
-            // one random number at most: the Russian roulette of a small residual
-            // estimate, or the optical thickness of a new ray
-            const bool roul = resid && t_sun < kSunRoulette;
-            if (roul || starting)
-                rng.need(1, (uint32_t)pix, A.sample_base + (uint32_t)s, A.stream_base + (uint32_t)job, A.key0, A.key1);
-            if (roul) t_sun = rng.take() * kSunRoulette < t_sun ? kSunRoulette : 0.0f;
+            bool locate = phase == kPhRay, trunc = false;
+            const bool hit = locate;
             if (crossing) {
-                tau -= r.khat * (r.texit - r.t);
-                if (resid && t_sun == 0.0f) {
-                    res = kReal;                    // the estimate is zero: the sun ray ends here
-                    phase = kPhEvent;
-                } else if (!step_cell(g, r)) {
-                    res = kExit;
-                    phase = kPhEvent;
-                } else {
-                    locate = true;
+                const float dt = r.texit - r.t;
+                tau -= r.khat * dt;
+                if (resid) {
+                    t_sun *= __expf(-(r.kmin + path_kg()) * dt);
+                    if (t_sun < kSunRoulette) {     // Russian roulette on small estimates
+                        rng.need(1, (uint32_t)pix, A.sample_base + (uint32_t)s, A.stream_base + (uint32_t)job, A.key0, A.key1);
+                        t_sun = rng.take() * kSunRoulette < t_sun ? kSunRoulette : 0.0f;
+                    }
                 }
-            } else if (starting) {
-                const float o[3] = {r.o[0], r.o[1], r.o[2]};
-                const float rd[3] = {shadow ? sun[0] : pd[0], shadow ? sun[1] : pd[1], shadow ? sun[2] : pd[2]};
-                if (ray_setup(g, r, o, rd, 0.0f)) {
-                    hit = true;
-                    // the start voxel is located afresh: keeping the event's voxel
-                    // per lane to skip this lookup cost six registers through the
-                    // whole loop, which cost more than the lookups
-                    locate = true;
-                } else {
-                    // misses the box: the next step finds the ray outside
-                    r.t = r.tend = r.texit = 0.0f;
-                    r.khat = 0.0f;
-                    r.kmin = 0.0f;
-                    r.lev = g.L;
-                }
+                // the ray ends here when its estimate is zero or it leaves the box
+                const bool spent = resid && t_sun == 0.0f;
+                res = spent ? kReal : kExit;
+                const bool inside = step_cell(g, r);
+                locate = inside && !spent;
+                phase = locate ? phase : kPhEvent;
             }
             if (locate) {
                 uint32_t nr = 0;   // (counted by ballot below when statistics are on)
-                locate_voxel(g, ns, r, A.op.mscale, nr);
-            }
-            if (locate) leaf_exit(g, r);
-            if (crossing && locate) {
-                leaf = true;
-                if (resid) r.khat = fmaxf(r.khat - (g.kscale * r.kmin + path_kg()), 0.0f);
+                locate_voxel<true>(g, ns, r, A.op.mscale, nr);
+                leaf_exit(g, r);
+                if (kSun == 2 && shadow) r.khat = fmaxf(r.khat - (r.kmin + path_kg()), 0.0f);
                 phase = voxel_phase(r, tau);
-                if (++segs >= A.op.max_segments) {
+                if (crossing && ++segs >= A.op.max_segments) {
                     trunc = true;
                     phase = kPhSample;      // stop the path
                 }
-            }
-            if (starting) {
-                if (kSun != 0 && shadow) {
-                    t_sun = 1.0f;
-                    if (kSun == 2) r.khat = fmaxf(r.khat - (g.kscale * r.kmin + path_kg()), 0.0f);
-                }
-                tau = rng.take_exp1();
-                phase = voxel_phase(r, tau);
             }
             if (stats) {
                 // memory reads of a voxel lookup: the cell, the ancestry mask, and the
@@ -1392,10 +1363,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
                 if (g.L >= 1) wave_count(cnt, kCReads, locate);
                 wave_count(cnt, kCReads, locate && r.lev >= 1 && r.lev < ns.lds_first);
                 wave_count(cnt, kCSegments, crossing);
-                wave_count(cnt, kCLeaf, leaf || hit);
-                wave_count(cnt, kCDeep, (leaf || hit) && r.lev < ns.lds_first);
+                wave_count(cnt, kCLeaf, locate);
+                wave_count(cnt, kCDeep, locate && r.lev < ns.lds_first);
                 wave_count(cnt, kCTrunc, trunc);
-                wave_count(cnt, kCNee, starting && shadow);
             }
         } else if (run == kPhCollide) {
             // ---- tentative collision in the current voxel: real or null
@@ -1409,11 +1379,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
                 rng.need(2, (uint32_t)pix, A.sample_base + (uint32_t)s, A.stream_base + (uint32_t)job, A.key0, A.key1);
                 const float t0 = r.t;
                 r.t = fminf(r.t + tau * __builtin_amdgcn_rcpf(r.khat), r.texit);
-                const float kmin = g.kscale * r.kmin + path_kg();
+                const float kmin = r.kmin + path_kg();
                 const float kctrl = kSun == 2 ? kmin : 0.0f;
                 float kx = kmin;                // a level-0 voxel is one cell: k is known
                 if (r.lev != 0) {
-                    kx = g.kscale * g.kc[collision_cell(g, r, r.t)] + path_kg();
+                    kx = g.kc[collision_cell(g, r, r.t)] + path_kg();
                     gathered = true;
                 }
                 t_sun *= __expf(-kctrl * (r.t - t0)) * fmaxf(0.0f, 1.0f - (kx - kctrl) * __builtin_amdgcn_rcpf(r.khat));
@@ -1440,7 +1410,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
                 rng.need(2, (uint32_t)pix, A.sample_base + (uint32_t)s, A.stream_base + (uint32_t)job, A.key0, A.key1);
                 r.t = fminf(r.t + tau * __builtin_amdgcn_rcpf(r.khat), r.texit);
                 const float thr = rng.take() * r.khat;
-                if (shadow && thr < g.kscale * r.kmin + path_kg()) {
+                if (shadow && thr < r.kmin + path_kg()) {
                     real = true;                // below the voxel's minimum: real without reading k
                 } else {
                     if (r.lev == 0) {
@@ -1449,7 +1419,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
                         kc_hit = g.kc[collision_cell(g, r, r.t)];
                             gathered = true;
                     }
-                    real = thr < g.kscale * kc_hit + path_kg();
+                    real = thr < kc_hit + path_kg();
                 }
                 if (real) {
                     res = kReal;
@@ -1490,7 +1460,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
                         pd[a] = r.d[a];
                         r.o[a] = r.o[a] + r.t * r.d[a];
                     }
-                    const float kd = g.kscale * kc_hit;
+                    const float kd = kc_hit;
                     kev = kd + path_kg();
                     const float ssa = NC_R(ssa) * kd * __builtin_amdgcn_rcpf(kd + path_kg());
                     float gain = 1.0f;
@@ -1515,7 +1485,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
                         phase = kPhSample;
                     } else if (w_nee > 0.0f) {
                         shadow = true;
-                        phase = kPhRay;
+                        start = true;
                     } else {
                         cont = true;
                     }
@@ -1548,7 +1518,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
                         phase = kPhSample;
                     } else if (w_nee > 0.0f) {
                         shadow = true;
-                        phase = kPhRay;
+                        start = true;
                     } else {
                         cont = true;
                     }
@@ -1581,7 +1551,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
                             lambert(pd, u1, u2);
                         else
                             turn(pd, kExt ? phase_sample_mu(hg, A.op.tab, u1) : hg_sample_mu(hg, u1), u2);
-                        phase = kPhRay;
+                        start = true;
                         if (kMode == kCollect && !ground_ev) {
                             // training record: vertex, incoming and outgoing directions, radiance so far
                             const unsigned long long k = atomicAdd(A.col.count, 1ull);
@@ -1656,7 +1626,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
                     pd[1] = d1;
                     pd[2] = d2;
                     beta *= wf;
-                    phase = kPhRay;
+                    start = true;
                 }
                 wave_sync();
             }
@@ -1796,7 +1766,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
                 segs = 0;
                 shadow = false;
                 traced = true;
-                phase = kPhRay;
+                start = true;
                 if (J.cam.type == 2) {
                     // irradiance sensor: first the sun's direct beam (a sun ray of
                     // weight 1), then, as after a ground reflection that always
@@ -1821,6 +1791,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
                     ground_ev = true;
                     shadow = true;
                 }
+            }
+        }
+        if (run != kPhCross && run != kPhCollide) {
+            // ---- rays started by this trip's events, scatterings and samples:
+            // here 20 lanes set theirs up at once; at the top of a step trip, where
+            // only the rays of one earlier trip wait, it was 7
+            if (stats) wave_count(cnt, kCNee, start && shadow);
+            if (start) {
+                rng.need(1, (uint32_t)pix, A.sample_base + (uint32_t)s, A.stream_base + (uint32_t)job, A.key0, A.key1);
+                const float o[3] = {r.o[0], r.o[1], r.o[2]};
+                const float rd[3] = {shadow ? sun[0] : pd[0], shadow ? sun[1] : pd[1], shadow ? sun[2] : pd[2]};
+                phase = kPhRay;
+                if (!ray_setup(g, r, o, rd, 0.0f)) {
+                    // misses the box: the next step finds the ray outside
+                    r.t = r.tend = r.texit = 0.0f;
+                    r.khat = 0.0f;
+                    r.kmin = 0.0f;
+                    r.lev = g.L;
+                    phase = kPhCross;
+                }
+                if (kSun != 0 && shadow) t_sun = 1.0f;
+                tau = rng.take_exp1();
             }
         }
         if (stats && lane == 0) atomicAdd(s_cnt + kCCycles0 + run, (unsigned long long)(wall_clock64() - t_trip));
@@ -2038,13 +2030,13 @@ hipError_t launch_render(const nc_ctx *ctx, const nc_grid *g, const float *d_kc,
                         : (const void *)render_kernel<4, kCollect, 2, false>;
     } else if (est == 0) {
         fn = wpe == 3   ? (const void *)render_kernel<3, kPlain, 0, false>
-             : wpe == 4 ? (const void *)render_kernel<4, kPlain, 0, false>
+             : wpe == 4 ? (const void *)render_kernel<6, kPlain, 0, false>
              : wpe == 5 ? (const void *)render_kernel<5, kPlain, 0, false>
                         : (const void *)render_kernel<6, kPlain, 0, false>;
     } else if (est == 1) {
-        fn = wpe == 3 ? (const void *)render_kernel<3, kPlain, 1, false> : (const void *)render_kernel<4, kPlain, 1, false>;
+        fn = wpe == 3 ? (const void *)render_kernel<3, kPlain, 1, false> : (const void *)render_kernel<6, kPlain, 1, false>;
     } else {
-        fn = wpe == 3 ? (const void *)render_kernel<3, kPlain, 2, false> : (const void *)render_kernel<4, kPlain, 2, false>;
+        fn = wpe == 3 ? (const void *)render_kernel<3, kPlain, 2, false> : (const void *)render_kernel<6, kPlain, 2, false>;
     }
     int resident = 0;
     const size_t lds = node_bytes + guide_bytes;
@@ -2158,6 +2150,8 @@ GridView grid_view(const nc_grid *g, const float *d_kc)
     v.L = g->L;
     v.k_gas = (float)g->params.k_gas;
     v.kscale = 1.0f;
+    v.narrow = g->L >= 1 && (long long)g->n[0] * g->n[1] < (1ll << 24) &&
+               (long long)g->n[0] * g->n[1] * g->n[2] < (1ll << 30);
     v.kc = d_kc;
     v.nodes = g->d_nodes;
     v.off = g->d_off;

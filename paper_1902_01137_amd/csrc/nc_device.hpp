@@ -149,6 +149,9 @@ struct RngBuf {
             left = 4;
         }
     }
+    // drop a block that holds fewer than k numbers, as need(k) does; the next
+    // one is computed when it is first needed
+    __device__ void skip(int k) { left = left < k ? 0 : left; }
     __device__ float take()
     {
         const uint32_t v = q0;
@@ -268,34 +271,26 @@ struct Ray {
     int xmask;           // axes whose voxel face is met at texit (bit a)
 };
 
-// 1 / d rounded to nearest, NaN for d = 0.  v_rcp_f32 and one Newton step in
-// FMAs give the correctly rounded reciprocal of every normal |d| < 2^126
-// (checked over all mantissas and exponents) in 3 instructions where the IEEE
-// division takes 10; other d (the caller's `odd`) take the division.
-__host__ __device__ inline float ray_inv(float d, bool odd)
+// Per axis 1 / d rounded to nearest, NaN for d = 0.  v_rcp_f32 and one Newton
+// step in FMAs give the correctly rounded reciprocal of every normal
+// |d| < 2^126 (checked over all mantissas and exponents) in 3 instructions
+// where the IEEE division takes 10; a direction with a subnormal component or
+// one of 2^126 or more takes the division.
+__host__ __device__ inline void ray_inverse(const float d[3], float inv[3])
 {
 #ifdef __HIP_DEVICE_COMPILE__
-    const float y = __builtin_amdgcn_rcpf(d);
-    float q = __builtin_fmaf(__builtin_fmaf(-d, y, 1.0f), y, y);
-    if (odd) q = d == 0.0f ? __builtin_nanf("") : 1.0f / d;
-    return q;
-#else
-    (void)odd;
-    return d == 0.0f ? __builtin_nanf("") : 1.0f / d;
-#endif
-}
-
-// a direction with a subnormal component or one of 2^126 or more
-__host__ __device__ inline bool ray_odd(const float d[3])
-{
-#ifdef __HIP_DEVICE_COMPILE__
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const float y = __builtin_amdgcn_rcpf(d[a]);
+        inv[a] = __builtin_fmaf(__builtin_fmaf(-d[a], y, 1.0f), y, y);
+    }
     const float m = fmaxf(fmaxf(fabsf(d[0]), fabsf(d[1])), fabsf(d[2]));
-    return __builtin_amdgcn_classf(d[0], 0x90) | __builtin_amdgcn_classf(d[1], 0x90) |
-           __builtin_amdgcn_classf(d[2], 0x90) | (m >= 0x1p126f);
-#else
-    (void)d;
-    return false;
+    if (!(__builtin_amdgcn_classf(d[0], 0x90) | __builtin_amdgcn_classf(d[1], 0x90) |
+          __builtin_amdgcn_classf(d[2], 0x90) | (m >= 0x1p126f)))
+        return;
 #endif
+#pragma unroll
+    for (int a = 0; a < 3; ++a) inv[a] = d[a] == 0.0f ? __builtin_nanf("") : 1.0f / d[a];
 }
 
 __host__ __device__ inline float face_t(const GridView &g, const Ray &r, int a, int j)
@@ -311,13 +306,12 @@ __host__ __device__ inline bool ray_setup(const GridView &g, Ray &r, const float
     float tin = tmin, tout = INFINITY;
     bool miss = false;
     float tlo[3];
-    const bool odd = ray_odd(d);
+    ray_inverse(d, r.inv);
     // per axis, as selects (lanes that disagree would run both sides of a branch)
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         r.o[a] = o[a];
         r.d[a] = d[a];
-        r.inv[a] = ray_inv(d[a], odd);
         // (both faces straight from the grid view, not through face_t: the
         // compiler cannot fold 0 h, and the hoisted per-axis values held through a
         // persistent loop cost registers)
@@ -336,9 +330,11 @@ __host__ __device__ inline bool ray_setup(const GridView &g, Ray &r, const float
     // matters for the walk, and the walk never steps back across a face
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const int j = clamp_int(floor_int((o[a] + tin * d[a] - g.lo[a]) * g.inv_h[a]), 0, g.n[a] - 1);
+        const int j = floor_int((o[a] + tin * d[a] - g.lo[a]) * g.inv_h[a]);
         const bool entered = (tin > tmin) & (tlo[a] == tin);   // entered through this axis' face
-        r.c[a] = entered ? (d[a] > 0.0f ? 0 : g.n[a] - 1) : j;
+        // (the far end by the clamp: the sign bit spread over the word, less its top bit)
+        const int end = (int)((uint32_t)(__builtin_bit_cast(int, d[a]) >> 31) >> 1);
+        r.c[a] = clamp_int(entered ? end : j, 0, g.n[a] - 1);
     }
     return true;
 }
@@ -468,12 +464,12 @@ __host__ __device__ inline bool next_leaf(const GridView &g, const NodeSrc &ns, 
     return true;
 }
 
-// Cell holding the point at parameter t, kept inside the current voxel so
-// that the gathered k never exceeds the voxel's majorant.  The voxel is found
+// k_c of the cell holding the point at parameter t, kept inside the current voxel
+// so that it never exceeds the voxel's majorant.  The voxel is found
 // from the next cell (which lies in its slab on every axis but those of the
 // exit face, one cell past it there), so that no register holds the current
 // cell between the crossing and a collision.
-__device__ inline size_t collision_cell(const GridView &g, const Ray &r, float t)
+__device__ inline float collision_k(const GridView &g, const Ray &r, float t)
 {
     const int l = r.lev;
     int cc[3];
@@ -485,8 +481,13 @@ __device__ inline size_t collision_cell(const GridView &g, const Ray &r, float t
         const int top = min(base + (1 << l), g.n[a]) - 1;
         cc[a] = clamp_int(floor_int((r.o[a] + t * r.d[a] - g.lo[a]) * g.inv_h[a]), base, top);
     }
+    if (g.narrow) {
+        const uint32_t cell = mad24((uint32_t)cc[2], (uint32_t)(g.n[0] * g.n[1]),
+                                    mad24((uint32_t)cc[1], (uint32_t)g.n[0], (uint32_t)cc[0]));
+        return *(const float *)((const char *)g.kc + (cell << 2));
+    }
     const uint32_t row = (uint32_t)cc[2] * (uint32_t)g.n[1] + (uint32_t)cc[1];
-    return (size_t)((uint64_t)row * (uint32_t)g.n[0] + (uint32_t)cc[0]);
+    return g.kc[(uint64_t)row * (uint32_t)g.n[0] + (uint32_t)cc[0]];
 }
 
 // ---------------------------------------------------------------------------
@@ -602,7 +603,7 @@ __device__ inline void turn_sc(float d[3], float mu, float sp, float cp)
     float n[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) n[k] = mu * d[k] + st * (cp * b1[k] + sp * b2[k]);
-    const float inv = rsqrtf(n[0] * n[0] + n[1] * n[1] + n[2] * n[2]);
+    const float inv = __builtin_amdgcn_rsqf(n[0] * n[0] + n[1] * n[1] + n[2] * n[2]);   // (|n|^2 is about 1)
 #pragma unroll
     for (int k = 0; k < 3; ++k) d[k] = n[k] * inv;
 }
@@ -679,7 +680,7 @@ __device__ inline int track_step_f(const GridView &g, const NodeSrc &ns, Ray &r,
             kc_hit = r.kmin;                  // a level-0 voxel is one cell: k is known
             real = thr < g.kscale * kc_hit + g.k_gas;
         } else {
-            kc_hit = g.kc[collision_cell(g, r, r.t)];
+            kc_hit = collision_k(g, r, r.t);
             ++reads;
             flags |= kFGather;
             real = thr < g.kscale * kc_hit + g.k_gas;

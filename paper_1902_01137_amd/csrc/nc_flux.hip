@@ -65,7 +65,7 @@ __device__ inline int track_step_scored(const GridView &g, const NodeSrc &ns, Ra
         if (r.lev == 0) {
             kc_hit = r.kmin;
         } else {
-            kc_hit = g.kc[collision_cell(g, r, r.t)];
+            kc_hit = collision_k(g, r, r.t);
             ++cnt.gathers;
         }
         const float k = g.kscale * kc_hit + g.k_gas;

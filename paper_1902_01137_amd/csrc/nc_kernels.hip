@@ -493,7 +493,7 @@ __device__ inline float ratio_transmittance(const GridView &g, const NodeSrc &ns
             const float kc = kctrl();
             float kx = g.kscale * r.kmin + g.k_gas;
             if (r.lev != 0) {
-                kx = g.kscale * g.kc[collision_cell(g, r, r.t)] + g.k_gas;
+                kx = g.kscale * collision_k(g, r, r.t) + g.k_gas;
                 ++cnt.gathers;
             }
             ++cnt.tentative;
@@ -634,6 +634,17 @@ __device__ inline void camera_ray(const CamView &c, int px, int py, float u1, fl
     }
 }
 
+// Lanes for which pred holds.  (The scalar count by hand: the compiler keeps
+// __popcll's result, and every comparison with it, in 64 bits, which the
+// scalar unit does not compare.)
+__device__ inline int lane_count(bool pred)
+{
+    const unsigned long long m = __ballot(pred);
+    int n;
+    asm("s_bcnt1_i32_b64 %0, %1" : "=s"(n) : "s"(m) : "scc");
+    return n;
+}
+
 __device__ inline unsigned int lanes_below(unsigned long long mask)
 {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
@@ -725,6 +736,12 @@ struct RenderArgs {
 // of diverging inside every traversal step.
 enum Phase { kPhCross = 0, kPhCollide = 1, kPhEvent = 2, kPhRay = 3, kPhSample = 4, kPhGuide = 5, kPhIdle = 6 };
 constexpr int kGuideMaxWait = 8;   // trips a partial tile of guided lanes may wait for more
+// Paths left in a wave, once the queues are drained, below which it runs every
+// phase in each trip.  505 k paths over a ragged field (a launch that is all
+// tail: its longest path scatters 2660 times): 13.8 ms with one phase a trip,
+// 11.9, 11.8 and 11.7 ms below 8, 16 and 64 lanes; 67 M paths lose from 64 (27.4
+// ms against 26.4 and 27.1: a wave still full of paths runs mostly empty phases).
+constexpr int kTailLanes = 16;
 enum RenderMode { kPlain = 0, kGuided = 1, kCollect = 2 };
 // ratio estimators: Russian roulette of a sun ray's estimate below this
 // transmissivity (survivors carry it).  On the cumulus view 0.25 reaches a
@@ -1286,11 +1303,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
     for (;;) {
         // lane counts per phase (scalar); a crossing step and the first voxel of
         // a new ray run in the same trip (the step phase)
-        const int n_step = __builtin_popcountll(__ballot((phase == kPhCross) | (phase == kPhRay)));
-        const int n_coll = __builtin_popcountll(__ballot(phase == kPhCollide));
-        const int n_event = __builtin_popcountll(__ballot(phase == kPhEvent));
-        const int n_sample = __builtin_popcountll(__ballot(phase == kPhSample));
-        const int n_guide = kMode == kGuided ? __builtin_popcountll(__ballot(phase == kPhGuide)) : 0;
+        const int n_step = lane_count((phase == kPhCross) | (phase == kPhRay));
+        const int n_coll = lane_count(phase == kPhCollide);
+        const int n_event = lane_count(phase == kPhEvent);
+        const int n_sample = lane_count(phase == kPhSample);
+        const int n_guide = kMode == kGuided ? lane_count(phase == kPhGuide) : 0;
         const int n_other = n_step + n_coll + n_event + n_sample;
         if (n_other + n_guide == 0) break;
         int run = kPhCross, best = n_step;
@@ -1312,325 +1329,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
                 ++guide_wait;
             }
         }
-        if (stats && lane == 0) {
-            atomicAdd(s_cnt + kCTrips0 + run, 1ull);
-            atomicAdd(s_cnt + kCLanes0 + run, (unsigned long long)best);
-        }
-        const long long t_trip = stats ? wall_clock64() : 0;
+        // Once the queues are drained the launch ends with the longest paths left,
+        // and a wave with few of them runs every phase in one trip, in the order
+        // a path goes through them: each lane then advances at every trip
+        // instead of waiting for its phase's turn.
+        const bool all = queue_done && n_other + n_guide <= kTailLanes;
+        const bool run_step = all || run == kPhCross, run_coll = all || run == kPhCollide;
+        const bool run_event = all || run == kPhEvent, run_sample = run == kPhSample || (all && n_sample > 0);
+        const bool run_guide = run == kPhGuide;
+        // statistics of a phase's trips: how many, their lanes, their clock ticks
+        long long t_trip = 0;
+        auto trip_begin = [&](int ph, bool in_phase) {
+            if (!stats) return;
+            const unsigned long long m = __ballot(in_phase);
+            if (lane == 0) {
+                atomicAdd(s_cnt + kCTrips0 + ph, m ? 1ull : 0ull);
+                atomicAdd(s_cnt + kCLanes0 + ph, (unsigned long long)(ph == kPhGuide ? best : __popcll(m)));
+            }
+            t_trip = wall_clock64();
+        };
+        auto trip_end = [&](int ph) {
+            if (stats && lane == 0) atomicAdd(s_cnt + kCCycles0 + ph, (unsigned long long)(wall_clock64() - t_trip));
+        };
         bool start = false;   // the lane starts a ray at the end of this trip (along pd, or towards the sun)
 
-        if (run == kPhCross) {
-            // ---- a step of the ordered crossing: lanes crossing into the next
-            // voxel (carrying the optical thickness) and lanes in the first
-            // cell of a new ray share the location of the voxel (ancestry mask,
-            // node) and its exit
-            const bool crossing = phase == kPhCross;
-            const bool resid = crossing && shadow && kSun == 2;
-            bool locate = phase == kPhRay, trunc = false;
-            const bool hit = locate;
-            if (crossing) {
-                const float dt = r.texit - r.t;
-                tau -= r.khat * dt;
-                if (resid) {
-                    t_sun *= __expf(-(r.kmin + path_kg()) * dt);
-                    if (t_sun < kSunRoulette) {     // Russian roulette on small estimates
-                        rng.need(1, (uint32_t)pix, A.sample_base + (uint32_t)s, A.stream_base + (uint32_t)job, A.key0, A.key1);
-                        t_sun = rng.take() * kSunRoulette < t_sun ? kSunRoulette : 0.0f;
-                    }
-                }
-                // the ray ends here when its estimate is zero or it leaves the box
-                const bool spent = resid && t_sun == 0.0f;
-                res = spent ? kReal : kExit;
-                const bool inside = step_cell(g, r);
-                locate = inside && !spent;
-                phase = locate ? phase : kPhEvent;
-            }
-            if (locate) {
-                uint32_t nr = 0;   // (counted by ballot below when statistics are on)
-                locate_voxel<true>(g, ns, r, A.op.mscale, nr);
-                leaf_exit(g, r);
-                if (kSun == 2 && shadow) r.khat = fmaxf(r.khat - (r.kmin + path_kg()), 0.0f);
-                phase = voxel_phase(r, tau);
-                if (crossing && ++segs >= A.op.max_segments) {
-                    trunc = true;
-                    phase = kPhSample;      // stop the path
-                }
-            }
-            if (stats) {
-                // memory reads of a voxel lookup: the cell, the ancestry mask, and the
-                // node when its level is not staged in LDS
-                wave_count(cnt, kCReads, locate);
-                if (g.L >= 1) wave_count(cnt, kCReads, locate);
-                wave_count(cnt, kCReads, locate && r.lev >= 1 && r.lev < ns.lds_first);
-                wave_count(cnt, kCSegments, crossing);
-                wave_count(cnt, kCLeaf, locate);
-                wave_count(cnt, kCDeep, locate && r.lev < ns.lds_first);
-                wave_count(cnt, kCTrunc, trunc);
-            }
-        } else if (run == kPhCollide) {
-            // ---- tentative collision in the current voxel: real or null
-            const bool active = phase == kPhCollide;
-            bool real = false, gathered = false, trunc = false;
-            if (active && shadow && kSun != 0) {
-                // ratio tracking (control 0) or residual ratio tracking (control
-                // = the voxel minimum; r.khat then holds the residual majorant):
-                // every tentative collision scales the estimate t_sun by
-                // 1 - (k - k_ctrl) / khat, the control part by exp(-k_ctrl dt)
-                rng.need(2, (uint32_t)pix, A.sample_base + (uint32_t)s, A.stream_base + (uint32_t)job, A.key0, A.key1);
-                const float t0 = r.t;
-                r.t = fminf(r.t + tau * __builtin_amdgcn_rcpf(r.khat), r.texit);
-                const float kmin = r.kmin + path_kg();
-                const float kctrl = kSun == 2 ? kmin : 0.0f;
-                float kx = kmin;                // a level-0 voxel is one cell: k is known
-                if (r.lev != 0) {
-                    kx = g.kc[collision_cell(g, r, r.t)] + path_kg();
-                    gathered = true;
-                }
-                t_sun *= __expf(-kctrl * (r.t - t0)) * fmaxf(0.0f, 1.0f - (kx - kctrl) * __builtin_amdgcn_rcpf(r.khat));
-                const float u = rng.take();
-                if (t_sun < kSunRoulette) {     // Russian roulette on small estimates
-                    if (u * kSunRoulette < t_sun)
-                        t_sun = kSunRoulette;
-                    else
-                        t_sun = 0.0f;
-                }
-                if (t_sun == 0.0f) {
-                    res = kReal;
-                    phase = kPhEvent;
-                    real = true;
-                } else {
-                    tau = rng.take_exp1();
-                    phase = voxel_phase(r, tau);
-                    if (++segs >= A.op.max_segments) {
-                        trunc = true;
-                        phase = kPhSample;
-                    }
-                }
-            } else if (active) {
-                rng.need(2, (uint32_t)pix, A.sample_base + (uint32_t)s, A.stream_base + (uint32_t)job, A.key0, A.key1);
-                r.t = fminf(r.t + tau * __builtin_amdgcn_rcpf(r.khat), r.texit);
-                const float thr = rng.take() * r.khat;
-                if (shadow && thr < r.kmin + path_kg()) {
-                    real = true;                // below the voxel's minimum: real without reading k
-                } else {
-                    if (r.lev == 0) {
-                        kc_hit = r.kmin;        // a level-0 voxel is one cell: k is known
-                    } else {
-                        kc_hit = g.kc[collision_cell(g, r, r.t)];
-                            gathered = true;
-                    }
-                    real = thr < kc_hit + path_kg();
-                }
-                if (real) {
-                    res = kReal;
-                    phase = kPhEvent;
-                } else {
-                    tau = rng.take_exp1();
-                    phase = voxel_phase(r, tau);
-                    if (++segs >= A.op.max_segments) {
-                        trunc = true;
-                        phase = kPhSample;
-                    }
-                }
-            }
-            if (stats) {
-                wave_count(cnt, kCSegments, active);
-                wave_count(cnt, kCTentative, active);
-                wave_count(cnt, kCReals, real);
-                wave_count(cnt, kCNulls, active && !real);
-                wave_count(cnt, kCGathers, gathered);
-                wave_count(cnt, kCTrunc, trunc);
-            }
-        } else if (run == kPhEvent) {
-            if (phase == kPhEvent) {
-                const HGc hg{NC_R(hg.a), NC_R(hg.b), NC_R(hg.c), NC_R(hg.e), NC_R(hg.d), NC_R(hg.r2g)};
-                const int max_scatter = NC_R(max_scatter);
-                // three numbers cover an event (absorption, then two for the new
-                // direction); a guided step takes absorption plus three
-                rng.need(kMode == kGuided ? 4 : 3, (uint32_t)pix, A.sample_base + (uint32_t)s,
-                         A.stream_base + (uint32_t)job, A.key0, A.key1);
-                bool cont = false;               // go on to the scatter / reflect decision
-                if (shadow) {
-                    if (res == kExit) Lp += beta * w_nee * (kSun != 0 ? t_sun : 1.0f);   // the sun ray got through
-                    cont = true;
-                } else if (res == kReal) {
-                    // volume event: local estimate of the sun, then scatter or absorb
-#pragma unroll
-                    for (int a = 0; a < 3; ++a) {
-                        pd[a] = r.d[a];
-                        r.o[a] = r.o[a] + r.t * r.d[a];
-                    }
-                    const float kd = kc_hit;
-                    kev = kd + path_kg();
-                    const float ssa = NC_R(ssa) * kd * __builtin_amdgcn_rcpf(kd + path_kg());
-                    float gain = 1.0f;
-                    if (kExt && A.op.cone) {
-                        // solar disc: the local estimate's direction drawn in its cone
-                        const JobView &J = NC_R(jobs)[job];
-                        const float s0[3] = {J.sun[0], J.sun[1], J.sun[2]};
-                        const float c1 = rng.take(), c2 = rng.take();
-                        float w[3];
-                        cone_dir(s0, A.op.cone_cos, c1, c2, w);
-                        sun[0] = w[0];
-                        sun[1] = w[1];
-                        sun[2] = w[2];
-                        gain = A.op.cone_gain;
-                    }
-                    const float mu = pd[0] * sun[0] + pd[1] * sun[1] + pd[2] * sun[2];
-                    w_nee = ssa * (kExt ? phase_eval(hg, A.op.tab, mu) : hg_phase(hg, mu)) * gain;
-                    p_cont = ssa;
-                    ground_ev = false;
-                    ++order;
-                    if (max_scatter >= 0 && order > max_scatter) {
-                        phase = kPhSample;
-                    } else if (w_nee > 0.0f) {
-                        shadow = true;
-                        start = true;
-                    } else {
-                        cont = true;
-                    }
-                } else if (r.d[2] < 0.0f) {
-                    // ground hit: Lambertian local estimate
-                    const float tg = -r.o[2] * __builtin_amdgcn_rcpf(r.d[2]);
-#pragma unroll
-                    for (int a = 0; a < 3; ++a) pd[a] = r.d[a];
-                    r.o[0] = r.o[0] + tg * r.d[0];
-                    r.o[1] = r.o[1] + tg * r.d[1];
-                    r.o[2] = 0.0f;
-                    const float rho = NC_R(jobs)[job].rho;
-                    float gain = 1.0f;
-                    if (kExt && A.op.cone) {
-                        const JobView &J = NC_R(jobs)[job];
-                        const float s0[3] = {J.sun[0], J.sun[1], J.sun[2]};
-                        const float c1 = rng.take(), c2 = rng.take();
-                        float w[3];
-                        cone_dir(s0, A.op.cone_cos, c1, c2, w);
-                        sun[0] = w[0];
-                        sun[1] = w[1];
-                        sun[2] = w[2];
-                        gain = A.op.cone_gain;
-                    }
-                    w_nee = rho * (1.0f / kPi) * sun[2] * gain;   // <= 0 (no sun ray) when the direction is below the horizon
-                    p_cont = rho;
-                    ground_ev = true;
-                    ++order;
-                    if (max_scatter >= 0 && order > max_scatter) {
-                        phase = kPhSample;
-                    } else if (w_nee > 0.0f) {
-                        shadow = true;
-                        start = true;
-                    } else {
-                        cont = true;
-                    }
-                } else {
-                    // escaped upward: a camera ray that met nothing may look into the solar disc
-                    if (kExt && A.op.cone && order == 0 && !ground_ev) {
-                        const JobView &J = NC_R(jobs)[job];
-                        if (r.d[0] * J.sun[0] + r.d[1] * J.sun[1] + r.d[2] * J.sun[2] >= A.op.cone_cos)
-                            Lp += beta * A.op.cone_L;
-                    }
-                    phase = kPhSample;
-                }
-                if (cont) {
-                    shadow = false;
-                    // (the disc's draw may have left too few numbers for the scattering)
-                    if (kExt && A.op.cone)
-                        rng.need(kMode == kGuided ? 4 : 3, (uint32_t)pix, A.sample_base + (uint32_t)s,
-                                 A.stream_base + (uint32_t)job, A.key0, A.key1);
-                    if (max_scatter >= 0 && order >= max_scatter) {
-                        phase = kPhSample;
-                    } else if (rng.take() >= p_cont) {
-                        phase = kPhSample;       // absorbed (volume) or not reflected (ground)
-                    } else if (kMode == kGuided && !ground_ev &&
-                               (A.guide_max_order == 0 || order <= A.guide_max_order)) {
-                        phase = kPhGuide;        // the network proposes the new direction (a later trip)
-                    } else {
-                        const float u1 = rng.take(), u2 = rng.take();
-                        const float win[3] = {pd[0], pd[1], pd[2]};
-                        if (ground_ev)
-                            lambert(pd, u1, u2);
-                        else
-                            turn(pd, kExt ? phase_sample_mu(hg, A.op.tab, u1) : hg_sample_mu(hg, u1), u2);
-                        start = true;
-                        if (kMode == kCollect && !ground_ev) {
-                            // training record: vertex, incoming and outgoing directions, radiance so far
-                            const unsigned long long k = atomicAdd(A.col.count, 1ull);
-                            if (k < A.col.cap) {
-                                float *q = A.col.records + k * kGuideRecord;
-#pragma unroll
-                                for (int a = 0; a < 3; ++a) {
-                                    q[a] = (r.o[a] - g.lo[a]) * A.gpos[a] - 1.0f;
-                                    q[3 + a] = win[a];
-                                    q[7 + a] = pd[a];
-                                }
-                                q[6] = __logf(1.0f + kev);
-                                q[10] = Lp;
-                                q[11] = __uint_as_float((uint32_t)(pix * A.col_spp + s));
-                            }
-                        }
-                    }
-                }
-            }
-        } else if (kMode == kGuided && run == kPhGuide) {
-            // ---- guided scattering: network inference on the matrix cores,
-            // then the MIS step in the same layout.  The first `best` waiting
-            // lanes (by rank) are packed into tiles of 16.
-            const bool waiting = phase == kPhGuide;
-            const unsigned long long want = __ballot(waiting);
-            const int rank = __popcll(want & ((1ull << lane) - 1ull));
-            const bool active = waiting && rank < best;
-            extern __shared__ __align__(16) float2 s_dyn[];
-            char *gb = reinterpret_cast<char *>(s_dyn) + A.guide_lds;
-            const short *wl = reinterpret_cast<const short *>(gb);
-            const float *bl = reinterpret_cast<const float *>(gb + kWOff[4] * 2);
-            char *wt = gb + kGuideWeightBytes + (threadIdx.x >> 6) * kGuideScratchPerWave;
-            short *tin = reinterpret_cast<short *>(wt);
-            float *tf = reinterpret_cast<float *>(wt + kGuideInBytes);
-            const int ntiles = (best + 15) >> 4;
-            const int row = rank & 15, col = lane & 15, kq = lane >> 4;
-            for (int t = 0; t < ntiles; ++t) {
-                const bool owner = active && (rank >> 4) == t;
-                if (owner) {
-                    float x[7];
-#pragma unroll
-                    for (int a = 0; a < 3; ++a) {
-                        x[a] = (r.o[a] - g.lo[a]) * A.gpos[a] - 1.0f;
-                        x[3 + a] = pd[a];
-                    }
-                    x[6] = __logf(1.0f + kev);
-                    put_guide_inputs(tin + row * 16, x);
-                    // the event trip left three numbers for this step
-                    float *f = tf + row * 8;
-                    const float u_sel = rng.take();
-                    f[0] = pd[0];
-                    f[1] = pd[1];
-                    f[2] = pd[2];
-                    f[3] = u_sel;
-                    f[4] = lobe_uniform(u_sel, A.guide_frac);
-                    f[5] = rng.take();   // u1
-                    f[6] = rng.take();   // u2
-                }
-                wave_sync();
-                float z[12];
-                guide_tile_forward(wl, bl, tin, lane, z);
-                const GuidedStep st = guided_turn_tile<kExt>(z, tf + col * 8, A.guide_frac,
-                                                                HGc{NC_R(hg.a), NC_R(hg.b), NC_R(hg.c), NC_R(hg.e),
-                                                                    NC_R(hg.d), NC_R(hg.r2g)},
-                                                                A.op.tab, kq);
-                // each owner takes its column's result
-                const int src = owner ? row : lane;
-                const float d0 = __shfl(st.d[0], src), d1 = __shfl(st.d[1], src), d2 = __shfl(st.d[2], src);
-                const float wf = __shfl(st.w, src);
-                if (owner) {
-                    pd[0] = d0;
-                    pd[1] = d1;
-                    pd[2] = d2;
-                    beta *= wf;
-                    start = true;
-                }
-                wave_sync();
-            }
-        } else {
+        if (run_sample) {
+            trip_begin(kPhSample, phase == kPhSample);
             // ---- finish the lane's path, then start its next sample or item
             bool need_item = false;
             if (phase == kPhSample) {
@@ -1792,8 +1516,206 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
                     shadow = true;
                 }
             }
+            trip_end(kPhSample);
         }
-        if (run != kPhCross && run != kPhCollide) {
+        if (run_event) {
+            trip_begin(kPhEvent, phase == kPhEvent);
+            if (phase == kPhEvent) {
+                const HGc hg{NC_R(hg.a), NC_R(hg.b), NC_R(hg.c), NC_R(hg.e), NC_R(hg.d), NC_R(hg.r2g)};
+                const int max_scatter = NC_R(max_scatter);
+                // three numbers cover an event (absorption, then two for the new
+                // direction); a guided step takes absorption plus three.  Lanes
+                // that go on to their sun ray first use none of them: theirs come
+                // with the ray's, below
+                constexpr int kEventDraws = kMode == kGuided ? 4 : 3;
+                if (kExt && A.op.cone) rng.need(kEventDraws, (uint32_t)pix, A.sample_base + (uint32_t)s, A.stream_base + (uint32_t)job, A.key0, A.key1);
+                bool cont = false;               // go on to the scatter / reflect decision
+                if (shadow) {
+                    if (res == kExit) Lp += beta * w_nee * (kSun != 0 ? t_sun : 1.0f);   // the sun ray got through
+                    cont = true;
+                } else if (res == kReal) {
+                    // volume event: local estimate of the sun, then scatter or absorb
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) {
+                        pd[a] = r.d[a];
+                        r.o[a] = r.o[a] + r.t * r.d[a];
+                    }
+                    const float kd = kc_hit;
+                    kev = kd + path_kg();
+                    const float ssa = NC_R(ssa) * kd * __builtin_amdgcn_rcpf(kd + path_kg());
+                    float gain = 1.0f;
+                    if (kExt && A.op.cone) {
+                        // solar disc: the local estimate's direction drawn in its cone
+                        const JobView &J = NC_R(jobs)[job];
+                        const float s0[3] = {J.sun[0], J.sun[1], J.sun[2]};
+                        const float c1 = rng.take(), c2 = rng.take();
+                        float w[3];
+                        cone_dir(s0, A.op.cone_cos, c1, c2, w);
+                        sun[0] = w[0];
+                        sun[1] = w[1];
+                        sun[2] = w[2];
+                        gain = A.op.cone_gain;
+                    }
+                    const float mu = pd[0] * sun[0] + pd[1] * sun[1] + pd[2] * sun[2];
+                    w_nee = ssa * (kExt ? phase_eval(hg, A.op.tab, mu) : hg_phase(hg, mu)) * gain;
+                    p_cont = ssa;
+                    ground_ev = false;
+                    ++order;
+                    if (max_scatter >= 0 && order > max_scatter) {
+                        phase = kPhSample;
+                    } else if (w_nee > 0.0f) {
+                        shadow = true;
+                        start = true;
+                    } else {
+                        cont = true;
+                    }
+                } else if (r.d[2] < 0.0f) {
+                    // ground hit: Lambertian local estimate
+                    const float tg = -r.o[2] * __builtin_amdgcn_rcpf(r.d[2]);
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) pd[a] = r.d[a];
+                    r.o[0] = r.o[0] + tg * r.d[0];
+                    r.o[1] = r.o[1] + tg * r.d[1];
+                    r.o[2] = 0.0f;
+                    const float rho = NC_R(jobs)[job].rho;
+                    float gain = 1.0f;
+                    if (kExt && A.op.cone) {
+                        const JobView &J = NC_R(jobs)[job];
+                        const float s0[3] = {J.sun[0], J.sun[1], J.sun[2]};
+                        const float c1 = rng.take(), c2 = rng.take();
+                        float w[3];
+                        cone_dir(s0, A.op.cone_cos, c1, c2, w);
+                        sun[0] = w[0];
+                        sun[1] = w[1];
+                        sun[2] = w[2];
+                        gain = A.op.cone_gain;
+                    }
+                    w_nee = rho * (1.0f / kPi) * sun[2] * gain;   // <= 0 (no sun ray) when the direction is below the horizon
+                    p_cont = rho;
+                    ground_ev = true;
+                    ++order;
+                    if (max_scatter >= 0 && order > max_scatter) {
+                        phase = kPhSample;
+                    } else if (w_nee > 0.0f) {
+                        shadow = true;
+                        start = true;
+                    } else {
+                        cont = true;
+                    }
+                } else {
+                    // escaped upward: a camera ray that met nothing may look into the solar disc
+                    if (kExt && A.op.cone && order == 0 && !ground_ev) {
+                        const JobView &J = NC_R(jobs)[job];
+                        if (r.d[0] * J.sun[0] + r.d[1] * J.sun[1] + r.d[2] * J.sun[2] >= A.op.cone_cos)
+                            Lp += beta * A.op.cone_L;
+                    }
+                    phase = kPhSample;
+                }
+                if (!cont) {
+                    if (!(kExt && A.op.cone)) rng.skip(kEventDraws);
+                } else {
+                    shadow = false;
+                    // (the disc's draw may have left too few numbers for the scattering)
+                    rng.need(kEventDraws, (uint32_t)pix, A.sample_base + (uint32_t)s, A.stream_base + (uint32_t)job, A.key0, A.key1);
+                    if (max_scatter >= 0 && order >= max_scatter) {
+                        phase = kPhSample;
+                    } else if (rng.take() >= p_cont) {
+                        phase = kPhSample;       // absorbed (volume) or not reflected (ground)
+                    } else if (kMode == kGuided && !ground_ev &&
+                               (A.guide_max_order == 0 || order <= A.guide_max_order)) {
+                        phase = kPhGuide;        // the network proposes the new direction (a later trip)
+                    } else {
+                        const float u1 = rng.take(), u2 = rng.take();
+                        const float win[3] = {pd[0], pd[1], pd[2]};
+                        if (ground_ev)
+                            lambert(pd, u1, u2);
+                        else
+                            turn(pd, kExt ? phase_sample_mu(hg, A.op.tab, u1) : hg_sample_mu(hg, u1), u2);
+                        start = true;
+                        if (kMode == kCollect && !ground_ev) {
+                            // training record: vertex, incoming and outgoing directions, radiance so far
+                            const unsigned long long k = atomicAdd(A.col.count, 1ull);
+                            if (k < A.col.cap) {
+                                float *q = A.col.records + k * kGuideRecord;
+#pragma unroll
+                                for (int a = 0; a < 3; ++a) {
+                                    q[a] = (r.o[a] - g.lo[a]) * A.gpos[a] - 1.0f;
+                                    q[3 + a] = win[a];
+                                    q[7 + a] = pd[a];
+                                }
+                                q[6] = __logf(1.0f + kev);
+                                q[10] = Lp;
+                                q[11] = __uint_as_float((uint32_t)(pix * A.col_spp + s));
+                            }
+                        }
+                    }
+                }
+            }
+            trip_end(kPhEvent);
+        }
+        if (kMode == kGuided && run_guide) {
+            trip_begin(kPhGuide, phase == kPhGuide);
+            // ---- guided scattering: network inference on the matrix cores,
+            // then the MIS step in the same layout.  The first `best` waiting
+            // lanes (by rank) are packed into tiles of 16.
+            const bool waiting = phase == kPhGuide;
+            const unsigned long long want = __ballot(waiting);
+            const int rank = __popcll(want & ((1ull << lane) - 1ull));
+            const bool active = waiting && rank < best;
+            extern __shared__ __align__(16) float2 s_dyn[];
+            char *gb = reinterpret_cast<char *>(s_dyn) + A.guide_lds;
+            const short *wl = reinterpret_cast<const short *>(gb);
+            const float *bl = reinterpret_cast<const float *>(gb + kWOff[4] * 2);
+            char *wt = gb + kGuideWeightBytes + (threadIdx.x >> 6) * kGuideScratchPerWave;
+            short *tin = reinterpret_cast<short *>(wt);
+            float *tf = reinterpret_cast<float *>(wt + kGuideInBytes);
+            const int ntiles = (best + 15) >> 4;
+            const int row = rank & 15, col = lane & 15, kq = lane >> 4;
+            for (int t = 0; t < ntiles; ++t) {
+                const bool owner = active && (rank >> 4) == t;
+                if (owner) {
+                    float x[7];
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) {
+                        x[a] = (r.o[a] - g.lo[a]) * A.gpos[a] - 1.0f;
+                        x[3 + a] = pd[a];
+                    }
+                    x[6] = __logf(1.0f + kev);
+                    put_guide_inputs(tin + row * 16, x);
+                    // the event trip left three numbers for this step
+                    float *f = tf + row * 8;
+                    const float u_sel = rng.take();
+                    f[0] = pd[0];
+                    f[1] = pd[1];
+                    f[2] = pd[2];
+                    f[3] = u_sel;
+                    f[4] = lobe_uniform(u_sel, A.guide_frac);
+                    f[5] = rng.take();   // u1
+                    f[6] = rng.take();   // u2
+                }
+                wave_sync();
+                float z[12];
+                guide_tile_forward(wl, bl, tin, lane, z);
+                const GuidedStep st = guided_turn_tile<kExt>(z, tf + col * 8, A.guide_frac,
+                                                                HGc{NC_R(hg.a), NC_R(hg.b), NC_R(hg.c), NC_R(hg.e),
+                                                                    NC_R(hg.d), NC_R(hg.r2g)},
+                                                                A.op.tab, kq);
+                // each owner takes its column's result
+                const int src = owner ? row : lane;
+                const float d0 = __shfl(st.d[0], src), d1 = __shfl(st.d[1], src), d2 = __shfl(st.d[2], src);
+                const float wf = __shfl(st.w, src);
+                if (owner) {
+                    pd[0] = d0;
+                    pd[1] = d1;
+                    pd[2] = d2;
+                    beta *= wf;
+                    start = true;
+                }
+                wave_sync();
+            }
+            trip_end(kPhGuide);
+        }
+        if (run_sample || run_event || run_guide) {
             // ---- rays started by this trip's events, scatterings and samples:
             // here 20 lanes set theirs up at once; at the top of a step trip, where
             // only the rays of one earlier trip wait, it was 7
@@ -1815,7 +1737,112 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
                 tau = rng.take_exp1();
             }
         }
-        if (stats && lane == 0) atomicAdd(s_cnt + kCCycles0 + run, (unsigned long long)(wall_clock64() - t_trip));
+        if (run_step) {
+            trip_begin(kPhCross, (phase == kPhCross) | (phase == kPhRay));
+            // ---- a step of the ordered crossing: lanes crossing into the next
+            // voxel (carrying the optical thickness) and lanes in the first
+            // cell of a new ray share the location of the voxel (ancestry mask,
+            // node) and its exit
+            const bool crossing = phase == kPhCross;
+            const bool resid = crossing && shadow && kSun == 2;
+            bool locate = phase == kPhRay, trunc = false;
+            const bool hit = locate;
+            if (crossing) {
+                const float dt = r.texit - r.t;
+                tau -= r.khat * dt;
+                if (resid) {
+                    t_sun *= __expf(-(r.kmin + path_kg()) * dt);
+                    if (t_sun < kSunRoulette) {     // Russian roulette on small estimates
+                        rng.need(1, (uint32_t)pix, A.sample_base + (uint32_t)s, A.stream_base + (uint32_t)job, A.key0, A.key1);
+                        t_sun = rng.take() * kSunRoulette < t_sun ? kSunRoulette : 0.0f;
+                    }
+                }
+                // the ray ends here when its estimate is zero or it leaves the box
+                const bool spent = resid && t_sun == 0.0f;
+                res = spent ? kReal : kExit;
+                const bool inside = step_cell(g, r);
+                locate = inside && !spent;
+                phase = locate ? phase : kPhEvent;
+            }
+            if (locate) {
+                uint32_t nr = 0;   // (counted by ballot below when statistics are on)
+                locate_voxel<true>(g, ns, r, A.op.mscale, nr);
+                leaf_exit(g, r);
+                if (kSun == 2 && shadow) r.khat = fmaxf(r.khat - (r.kmin + path_kg()), 0.0f);
+                phase = voxel_phase(r, tau);
+                if (crossing && ++segs >= A.op.max_segments) {
+                    trunc = true;
+                    phase = kPhSample;      // stop the path
+                }
+            }
+            if (stats) {
+                // memory reads of a voxel lookup: the cell, the ancestry mask, and the
+                // node when its level is not staged in LDS
+                wave_count(cnt, kCReads, locate);
+                if (g.L >= 1) wave_count(cnt, kCReads, locate);
+                wave_count(cnt, kCReads, locate && r.lev >= 1 && r.lev < ns.lds_first);
+                wave_count(cnt, kCSegments, crossing);
+                wave_count(cnt, kCLeaf, locate);
+                wave_count(cnt, kCDeep, locate && r.lev < ns.lds_first);
+                wave_count(cnt, kCTrunc, trunc);
+            }
+            trip_end(kPhCross);
+        }
+        if (run_coll) {
+            trip_begin(kPhCollide, phase == kPhCollide);
+            // ---- tentative collision in the current voxel: real or null
+            const bool active = phase == kPhCollide;
+            bool real = false, gathered = false, trunc = false;
+            if (active) {
+                rng.need(2, (uint32_t)pix, A.sample_base + (uint32_t)s, A.stream_base + (uint32_t)job, A.key0, A.key1);
+                const float t0 = r.t;
+                r.t = fminf(r.t + tau * __builtin_amdgcn_rcpf(r.khat), r.texit);
+                const float u = rng.take();
+                const float thr = u * r.khat;
+                const float kmin = r.kmin + path_kg();
+                // a sun ray by delta tracking is stopped below the voxel's minimum
+                // without reading k; a level-0 voxel is one cell: k is known
+                const bool below = kSun == 0 && shadow && thr < kmin;
+                float kx = r.kmin;
+                gathered = (r.lev != 0) & !below;
+                if (gathered) kx = collision_k(g, r, r.t);
+                if (kSun != 0 && shadow) {
+                    // ratio tracking (control 0) or residual ratio tracking (control
+                    // = the voxel minimum; r.khat then holds the residual majorant):
+                    // every tentative collision scales the estimate t_sun by
+                    // 1 - (k - k_ctrl) / khat, the control part by exp(-k_ctrl dt)
+                    const float kctrl = kSun == 2 ? kmin : 0.0f;
+                    t_sun *= __expf(-kctrl * (r.t - t0)) *
+                             fmaxf(0.0f, 1.0f - (kx + path_kg() - kctrl) * __builtin_amdgcn_rcpf(r.khat));
+                    if (t_sun < kSunRoulette)       // Russian roulette on small estimates
+                        t_sun = u * kSunRoulette < t_sun ? kSunRoulette : 0.0f;
+                    real = t_sun == 0.0f;
+                } else {
+                    if (!below) kc_hit = kx;
+                    real = below | (thr < kx + path_kg());
+                }
+                if (real) {
+                    res = kReal;
+                    phase = kPhEvent;
+                } else {
+                    tau = rng.take_exp1();
+                    phase = voxel_phase(r, tau);
+                    if (++segs >= A.op.max_segments) {
+                        trunc = true;
+                        phase = kPhSample;
+                    }
+                }
+            }
+            if (stats) {
+                wave_count(cnt, kCSegments, active);
+                wave_count(cnt, kCTentative, active);
+                wave_count(cnt, kCReals, real);
+                wave_count(cnt, kCNulls, active && !real);
+                wave_count(cnt, kCGathers, gathered);
+                wave_count(cnt, kCTrunc, trunc);
+            }
+            trip_end(kPhCollide);
+        }
     }
     if (!kSets || A.n_sets == 1) break;
     // every lane of this wave is idle: once all waves of the workgroup are, serve
@@ -1990,10 +2017,11 @@ hipError_t launch_render(const nc_ctx *ctx, const nc_grid *g, const float *d_kc,
     static_assert(sizeof(RenderRare) <= kRareBytes &&
                       kRareBytes <= (kScratchErr - kScratchRare) * sizeof(unsigned long long),
                   "scratch too small for the renderer parameters");
-    // register budget: waves per SIMD the kernel is compiled for (3..6)
-    // (default 4, a cap of 128 registers: the plain and collection kernels
-    // take 80-95, so the occupancy query then gives them 5-6 waves per SIMD;
-    // the guided ones fill the 128 with a few spilled)
+    // register budget: the plain kernels are compiled for 6 waves per SIMD (78
+    // of 80 registers, none spilled; 4 instead of 6 costs 15 %), or for 3 when
+    // the caller asks for few; the collection and extended ones for 4 (79-88
+    // registers, so 5-6 waves fit all the same), the guided ones for 4 (all of
+    // the 128 registers)
     const int wpe = ctx->launch.waves_per_cu > 0 ? std::max(3, std::min(6, ctx->launch.waves_per_cu / 4)) : 4;
     // kernel variant: mode, sun-ray estimator, register budget (waves per SIMD)
     const int est = s.flags & NC_SUN_ESTIMATOR_MASK;
@@ -2028,15 +2056,14 @@ hipError_t launch_render(const nc_ctx *ctx, const nc_grid *g, const float *d_kc,
         fn = est == 0 ? (const void *)render_kernel<4, kCollect, 0, false>
              : est == 1 ? (const void *)render_kernel<4, kCollect, 1, false>
                         : (const void *)render_kernel<4, kCollect, 2, false>;
-    } else if (est == 0) {
-        fn = wpe == 3   ? (const void *)render_kernel<3, kPlain, 0, false>
-             : wpe == 4 ? (const void *)render_kernel<6, kPlain, 0, false>
-             : wpe == 5 ? (const void *)render_kernel<5, kPlain, 0, false>
-                        : (const void *)render_kernel<6, kPlain, 0, false>;
-    } else if (est == 1) {
-        fn = wpe == 3 ? (const void *)render_kernel<3, kPlain, 1, false> : (const void *)render_kernel<6, kPlain, 1, false>;
+    } else if (wpe == 3) {
+        fn = est == 0   ? (const void *)render_kernel<3, kPlain, 0, false>
+             : est == 1 ? (const void *)render_kernel<3, kPlain, 1, false>
+                        : (const void *)render_kernel<3, kPlain, 2, false>;
     } else {
-        fn = wpe == 3 ? (const void *)render_kernel<3, kPlain, 2, false> : (const void *)render_kernel<6, kPlain, 2, false>;
+        fn = est == 0   ? (const void *)render_kernel<6, kPlain, 0, false>
+             : est == 1 ? (const void *)render_kernel<6, kPlain, 1, false>
+                        : (const void *)render_kernel<6, kPlain, 2, false>;
     }
     int resident = 0;
     const size_t lds = node_bytes + guide_bytes;

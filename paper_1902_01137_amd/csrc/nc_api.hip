@@ -258,7 +258,8 @@ hipError_t ensure_jobs(nc_ctx *ctx, size_t n)
 nc::RenderScratch ctx_render_scratch(const nc_ctx *ctx)
 {
     return nc::RenderScratch{(nc::JobView *)ctx->d_jobs, ctx->d_scratch + nc::kScratchRare,
-                             ctx->d_scratch + nc::kScratchQueues, nc::kMaxQueueSets};
+                             ctx->d_scratch + nc::kScratchQueues, nc::kMaxQueueSets,
+                             reinterpret_cast<uint32_t *>(ctx->d_scratch + nc::kScratchWords)};
 }
 
 struct DeviceGuard {
@@ -300,7 +301,9 @@ nc_status nc_ctx_create(int32_t device, void *hip_stream, nc_ctx **out)
     if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, device) == hipSuccess &&
         lds > 0)
         ctx->lds_per_cu = (size_t)lds;
-    e = hipMalloc(&ctx->d_scratch, sizeof(unsigned long long) * nc::kScratchWords);
+    // (the tail kernels' paths behind the scratch words)
+    e = hipMalloc(&ctx->d_scratch, sizeof(unsigned long long) * nc::kScratchWords +
+                                       sizeof(uint32_t) * (size_t)nc::kTailCap * nc::kTailWords);
     if (e != hipSuccess) {
         delete ctx;
         return hip_fail(nullptr, e, "hipMalloc(scratch)");

@@ -464,6 +464,18 @@ __host__ __device__ inline bool next_leaf(const GridView &g, const NodeSrc &ns, 
     return true;
 }
 
+// k_c of a cell
+__device__ inline float cell_k(const GridView &g, const int cc[3])
+{
+    if (g.narrow) {
+        const uint32_t cell = mad24((uint32_t)cc[2], (uint32_t)(g.n[0] * g.n[1]),
+                                    mad24((uint32_t)cc[1], (uint32_t)g.n[0], (uint32_t)cc[0]));
+        return *(const float *)((const char *)g.kc + (cell << 2));
+    }
+    const uint32_t row = (uint32_t)cc[2] * (uint32_t)g.n[1] + (uint32_t)cc[1];
+    return g.kc[(uint64_t)row * (uint32_t)g.n[0] + (uint32_t)cc[0]];
+}
+
 // k_c of the cell holding the point at parameter t, kept inside the current voxel
 // so that it never exceeds the voxel's majorant.  The voxel is found
 // from the next cell (which lies in its slab on every axis but those of the
@@ -481,13 +493,7 @@ __device__ inline float collision_k(const GridView &g, const Ray &r, float t)
         const int top = min(base + (1 << l), g.n[a]) - 1;
         cc[a] = clamp_int(floor_int((r.o[a] + t * r.d[a] - g.lo[a]) * g.inv_h[a]), base, top);
     }
-    if (g.narrow) {
-        const uint32_t cell = mad24((uint32_t)cc[2], (uint32_t)(g.n[0] * g.n[1]),
-                                    mad24((uint32_t)cc[1], (uint32_t)g.n[0], (uint32_t)cc[0]));
-        return *(const float *)((const char *)g.kc + (cell << 2));
-    }
-    const uint32_t row = (uint32_t)cc[2] * (uint32_t)g.n[1] + (uint32_t)cc[1];
-    return g.kc[(uint64_t)row * (uint32_t)g.n[0] + (uint32_t)cc[0]];
+    return cell_k(g, cc);
 }
 
 // ---------------------------------------------------------------------------
@@ -653,6 +659,55 @@ __device__ inline void flush_counters(const Counters &c, nc_counters *out)
     }
 }
 
+// Lanes for which pred holds.  (The scalar count by hand: the compiler keeps
+// __popcll's result, and every comparison with it, in 64 bits, which the
+// scalar unit does not compare.)
+__device__ inline int lane_count(bool pred)
+{
+    const unsigned long long m = __ballot(pred);
+    int n;
+    asm("s_bcnt1_i32_b64 %0, %1" : "=s"(n) : "s"(m) : "scc");
+    return n;
+}
+
+__device__ inline unsigned int lanes_below(unsigned long long mask)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+// Lane phases of the phase-scheduled kernels.  Each loop trip the wave runs the
+// phase that the most lanes are waiting in (ballot counts); the other lanes
+// wait.  Expensive code (events, ray starts, new samples) thus runs for many
+// lanes at once instead of diverging inside every traversal step.
+enum Phase { kPhCross = 0, kPhCollide = 1, kPhEvent = 2, kPhRay = 3, kPhSample = 4, kPhGuide = 5, kPhIdle = 6 };
+static_assert(kPhGuide == 5 && kPhIdle == 6, "six running phases, one counter slot each");
+// Queue items a wave takes per global atomic: one per lane, so that the last
+// chunks are short (paths differ a lot in cost and the launch ends with the
+// slowest wave).
+constexpr int kChunk = 64;
+static_assert(kChunk >= 64, "a chunk must cover every lane of a wave that needs an item");
+
+// After the optical thickness tau has been drawn or carried: a tentative
+// collision inside the current voxel, or a move to the next voxel.
+__device__ inline int voxel_phase(const Ray &r, float tau)
+{
+    return (r.khat > 0.0f && tau < r.khat * (r.texit - r.t)) ? kPhCollide : kPhCross;
+}
+
+// block-level event counters in LDS (same order as nc_counters)
+enum BlockCounter {
+    kCPaths = 0, kCSegments, kCTentative, kCNulls, kCReals, kCLeaf, kCGathers, kCReads, kCNee, kCTrunc,
+    kCTrips0, kCLanes0 = kCTrips0 + 6, kCCycles0 = kCLanes0 + 6, kCDeep = kCCycles0 + 6,
+    kNumBlockCounters = kCDeep + 1
+};
+
+__device__ inline void wave_count(unsigned long long *s_cnt, int k, bool pred)
+{
+    if (!s_cnt) return;   // no counters asked for
+    const unsigned long long m = __ballot(pred);
+    if (m && __lane_id() == 0) atomicAdd(s_cnt + k, (unsigned long long)__popcll(m));
+}
+
 // ===========================================================================
 // One step of null-collision tracking in the piecewise-constant majorant
 // (Section 2.3 and Eq. 2, with the optical thickness tau carried from voxel
@@ -735,6 +790,26 @@ __device__ inline void start_ray(const GridView &g, const NodeSrc &ns, Ray &r, c
     }
 }
 
+// The level offsets and the staged levels' nodes into LDS; rows (may be
+// null): the level table of locate_voxel.  Ends with a block barrier.
+__device__ inline void stage_levels(const GridView &g, int lds_first, int lds_nodes, float2 *s_nodes, int *s_off,
+                                    int4 *rows = nullptr)
+{
+    for (int i = threadIdx.x; i < NC_MAX_LEVELS + 2; i += blockDim.x) {
+        s_off[i] = i <= g.L + 1 ? g.off[i] : 0;
+        if (rows) {
+            const int d0 = level_dim(g.n[0], min(i, 30)), d1 = level_dim(g.n[1], min(i, 30));
+            const int base = i >= lds_first && i <= g.L ? g.off[lds_first] : 0;
+            rows[i] = make_int4(i <= g.L ? g.off[i] - base : 0, d0, d0 * d1, 0);
+        }
+    }
+    if (lds_nodes > 0) {
+        const int base = g.off[lds_first];
+        for (int i = threadIdx.x; i < lds_nodes; i += blockDim.x) s_nodes[i] = g.nodes[base + i];
+    }
+    __syncthreads();
+}
+
 // The voxel a ray was in when it stopped at an event; a new ray leaving the
 // event point starts in the same voxel unless rounding put its origin in a
 // neighbouring cell, which the check below detects.
@@ -774,25 +849,264 @@ __device__ inline void start_ray_cached(const GridView &g, const NodeSrc &ns, Ra
     }
 }
 
-// The level offsets and the staged levels' nodes into LDS; rows (may be
-// null): the level table of locate_voxel.  Ends with a block barrier.
-__device__ inline void stage_levels(const GridView &g, int lds_first, int lds_nodes, float2 *s_nodes, int *s_off,
-                                    int4 *rows = nullptr)
+// ---------------------------------------------------------------------------
+// A path on four lanes.  A wave that holds one path advances it by one
+// instruction every 6 to 8 cycles whatever the instruction (measured: dependent
+// FMAs 8.3 cycles, scalar adds 8, independent adds 6), so a lone path's speed is
+// its instruction count.  Three of the four lanes of a quad therefore hold an
+// axis each (the fourth repeats x), so what a ray does per axis is one
+// instruction instead of three; minima and sums over the axes are two quad
+// permutes; everything else is the same in the four lanes.  All branches are
+// on values that are the same in the quad.  The arithmetic is the one-lane
+// walk's, operation for operation (the order of a sum over the axes included),
+// so a path may be handed from one form to the other at any point.  Narrow
+// grids only (GridView::narrow).
+// ---------------------------------------------------------------------------
+template <int kCtrl>
+__device__ inline int quad_perm(int x)
 {
-    for (int i = threadIdx.x; i < NC_MAX_LEVELS + 2; i += blockDim.x) {
-        s_off[i] = i <= g.L + 1 ? g.off[i] : 0;
-        if (rows) {
-            const int d0 = level_dim(g.n[0], min(i, 30)), d1 = level_dim(g.n[1], min(i, 30));
-            const int base = i >= lds_first && i <= g.L ? g.off[lds_first] : 0;
-            rows[i] = make_int4(i <= g.L ? g.off[i] - base : 0, d0, d0 * d1, 0);
+    return __builtin_amdgcn_mov_dpp(x, kCtrl, 0xf, 0xf, true);
+}
+template <int kCtrl>
+__device__ inline float quad_perm(float x)
+{
+    return __int_as_float(quad_perm<kCtrl>(__float_as_int(x)));
+}
+constexpr int kQuadSwap1 = 0xb1, kQuadSwap2 = 0x4e;   // lane ^ 1, lane ^ 2
+// the value of axis kAxis, in all four lanes
+template <int kAxis, class T>
+__device__ inline T quad_axis(T x)
+{
+    return quad_perm<kAxis * 0x55>(x);
+}
+__device__ inline float quad_min(float x)
+{
+    x = fminf(x, quad_perm<kQuadSwap1>(x));
+    return fminf(x, quad_perm<kQuadSwap2>(x));
+}
+__device__ inline float quad_max(float x)
+{
+    x = fmaxf(x, quad_perm<kQuadSwap1>(x));
+    return fmaxf(x, quad_perm<kQuadSwap2>(x));
+}
+__device__ inline int quad_add(int x)
+{
+    x += quad_perm<kQuadSwap1>(x);
+    return x + quad_perm<kQuadSwap2>(x);
+}
+__device__ inline int quad_or(int x)
+{
+    x |= quad_perm<kQuadSwap1>(x);
+    return x | quad_perm<kQuadSwap2>(x);
+}
+// x[0] + x[1] + x[2], summed in that order
+__device__ inline float quad_sum(float x) { return quad_axis<0>(x) + quad_axis<1>(x) + quad_axis<2>(x); }
+
+// The axis' value of three.  (By value: a choice between members of a record
+// becomes an address into it, which puts the whole record in scratch memory.)
+template <class T>
+__device__ inline T quad_pick(int ax, T x, T y, T z)
+{
+    return ax == 0 ? x : ax == 1 ? y : z;
+}
+
+// The lane's axis of the grid.
+struct QuadGrid {
+    int ql, ax;          // lane of the quad, its axis (lane 3: x again)
+    float lo, hi, h, inv_h;
+    int n;
+    int cell_stride, mask_stride;   // of the axis (lane 3: 0, it takes no part in the sums)
+    const int4 *rows;    // LDS: per level nodes per row and slice, and the level's offset
+
+    __device__ __attribute__((always_inline)) void init(const GridView &g, const int4 *rows_)
+    {
+        ql = (int)(threadIdx.x & 3u);
+        ax = ql == 3 ? 0 : ql;
+        lo = quad_pick(ax, g.lo[0], g.lo[1], g.lo[2]);
+        hi = quad_pick(ax, g.hi[0], g.hi[1], g.hi[2]);
+        h = quad_pick(ax, g.h[0], g.h[1], g.h[2]);
+        inv_h = quad_pick(ax, g.inv_h[0], g.inv_h[1], g.inv_h[2]);
+        n = quad_pick(ax, g.n[0], g.n[1], g.n[2]);
+        const int d0 = level_dim(g.n[0], 1), d1 = level_dim(g.n[1], 1);
+        cell_stride = ql == 0 ? 1 : ql == 1 ? g.n[0] : ql == 2 ? g.n[0] * g.n[1] : 0;
+        mask_stride = ql == 0 ? 1 : ql == 1 ? d0 : ql == 2 ? d0 * d1 : 0;
+        rows = rows_;
+    }
+};
+
+// A ray on a quad: per axis o, d, inv, the cell and its voxel's faces; the rest as in Ray.
+struct QuadRay {
+    float o, d, inv, tf;
+    int c, clo, chi;         // current cell; its voxel's first cell and the one past its last
+    float t, tend, te, texit;
+    float khat, kmin;
+    int lev;
+    // a cell of a voxel known before (an event's, or the one its sun ray started in)
+    int vc, vlev;
+    float vkmin, vkhat;
+
+    // as ray_setup
+    __device__ __attribute__((always_inline)) bool setup(const QuadGrid &g, float dir)
+    {
+        d = dir;
+        {
+            const float y = __builtin_amdgcn_rcpf(d);
+            inv = __builtin_fmaf(__builtin_fmaf(-d, y, 1.0f), y, y);
+            if (__builtin_amdgcn_classf(d, 0x90) | (fabsf(d) >= 0x1p126f)) {
+                asm volatile("");   // (a branch: the division is not to be computed beside the short form)
+                inv = 1.0f / d;
+            }
+        }
+        const float t0 = (g.lo - o) * inv, t1 = (g.hi - o) * inv;
+        float tlo = t0 > t1 ? t1 : t0;
+        // parallel to the axis' faces and outside their slab: a miss
+        const bool out = (d == 0.0f) & ((o < g.lo) | (o > g.hi));
+        const float tin = fmaxf(0.0f, quad_max(out ? INFINITY : tlo));
+        const float tout = quad_min(t0 > t1 ? t0 : t1);
+        if (!(tin < tout)) return false;
+        t = tin;
+        tend = tout;
+        const int j = floor_int((o + tin * d - g.lo) * g.inv_h);
+        const bool entered = (tin > 0.0f) & (tlo == tin);
+        const int end = (int)((uint32_t)(__float_as_int(d) >> 31) >> 1);
+        c = clamp_int(entered ? end : j, 0, g.n - 1);
+        return true;
+    }
+    // the current voxel's exit faces and parameter (as leaf_exit), from its level and a cell
+    __device__ __attribute__((always_inline)) void faces(const QuadGrid &g)
+    {
+        clo = (c >> lev) << lev;
+        chi = min(clo + (1 << lev), g.n);
+        tf = ((float)(d > 0.0f ? chi : clo) * g.h + g.lo - o) * inv;
+        te = fminf(tend, quad_min(tf));
+    }
+    __device__ __attribute__((always_inline)) void enter(const QuadGrid &g)
+    {
+        faces(g);
+        texit = te < t ? t : te;
+    }
+    // across the exit face (t is there already): the next cell
+    __device__ __attribute__((always_inline)) void next_cell(const QuadGrid &g)
+    {
+        const int j = clamp_int(floor_int((o + t * d - g.lo) * g.inv_h), clo, chi - 1);
+        c = tf == te ? (d > 0.0f ? chi : clo - 1) : j;
+    }
+    // k_c of the cell at parameter t (as collision_k)
+    __device__ __attribute__((always_inline)) float k_at(const GridView &gv, const QuadGrid &g) const
+    {
+        const int cc = clamp_int(floor_int((o + t * d - g.lo) * g.inv_h), clo, chi - 1);
+        const uint32_t cell = (uint32_t)quad_add((int)mad24((uint32_t)cc, (uint32_t)g.cell_stride, 0u));
+        return *(const float *)((const char *)gv.kc + (cell << 2));
+    }
+    // as locate_voxel
+    __device__ __attribute__((always_inline)) void locate(const GridView &gv, const QuadGrid &g, const NodeSrc &ns,
+                                                          float mscale)
+    {
+        const uint32_t cell = (uint32_t)quad_add((int)mad24((uint32_t)c, (uint32_t)g.cell_stride, 0u));
+        const uint32_t mi = (uint32_t)quad_add((int)mad24((uint32_t)c >> 1, (uint32_t)g.mask_stride, 0u));
+        const float kcell = *(const float *)((const char *)gv.kc + (cell << 2));
+        const uint32_t m = *(const uint16_t *)((const char *)gv.mask + (mi << 1));
+        lev = 31 - __builtin_clz(m | 1u);
+        float kmax = kcell;
+        kmin = kcell;
+        if (lev != 0) {
+            const int4 row = g.rows[lev];
+            const int stride = g.ql == 3 ? 0 : quad_pick(g.ql, 1, row.y, row.z);
+            const uint32_t idx =
+                (uint32_t)row.x + (uint32_t)quad_add((int)mad24((uint32_t)(c >> lev), (uint32_t)stride, 0u));
+            float2 nd;
+            if (lev >= ns.lds_first) {
+                nd = ns.lds[idx];
+                asm volatile("" : "+v"(nd.x), "+v"(nd.y));   // (two loads, as in locate_voxel)
+            } else {
+                nd = *(const float2 *)((const char *)ns.glob + (idx << 3));
+            }
+            kmin = node_kmin(nd);
+            kmax = nd.y;
+        }
+        khat = mscale * (gv.kscale * kmax + gv.k_gas);
+    }
+    // the voxel of the ray's first cell: the known one, if the cell lies in it (then nothing is read)
+    __device__ __attribute__((always_inline)) void first_voxel(const GridView &gv, const QuadGrid &g,
+                                                               const NodeSrc &ns, float mscale)
+    {
+        lev = vlev;
+        kmin = vkmin;
+        khat = vkhat;
+        if ((quad_or(c ^ vc) >> vlev) != 0) locate(gv, g, ns, mscale);
+        keep_voxel();
+    }
+    __device__ __attribute__((always_inline)) void keep_voxel()
+    {
+        vc = c;
+        vlev = lev;
+        vkmin = kmin;
+        vkhat = khat;
+    }
+};
+
+// A path's random numbers on a quad: its lanes compute four consecutive blocks
+// at once (a quarter of the Philox instructions per block) into the quad's 16
+// words of LDS, from where a block is read when its numbers are first needed.
+// The same stream as RngBuf and Rng.
+struct RngQuad {
+    uint32_t *buf;               // the quad's words
+    uint32_t draw;               // next block
+    uint32_t q0, q1, q2, q3;
+    int left;
+
+    __device__ __attribute__((always_inline)) void block(uint32_t a, uint32_t b, uint32_t stream, uint32_t k0,
+                                                         uint32_t k1, bool fill)
+    {
+        if (fill) {
+            const uint32_t ql = threadIdx.x & 3u;
+            const U4 r = philox4x32_10_uk(U4{a, b, (draw & ~3u) + ql, stream}, k0, k1);
+            *reinterpret_cast<uint4 *>(buf + 4u * ql) = make_uint4(r.x, r.y, r.z, r.w);
+            // (lanes of one wave: LDS operations complete in order)
+            __builtin_amdgcn_wave_barrier();
+        }
+        const uint4 v = *reinterpret_cast<const uint4 *>(buf + 4u * (draw & 3u));
+        q0 = v.x;
+        q1 = v.y;
+        q2 = v.z;
+        q3 = v.w;
+        ++draw;
+    }
+    // continue a stream at block draw_ with left_ numbers of the block before it to come
+    __device__ void resume(uint32_t draw_, int left_, uint32_t a, uint32_t b, uint32_t stream, uint32_t k0, uint32_t k1)
+    {
+        draw = draw_;
+        left = left_;
+        if (left_ > 0) --draw;
+        if (left_ > 0 || (draw & 3u)) {
+            const uint32_t at = draw;
+            block(a, b, stream, k0, k1, true);
+            draw = at + (left_ > 0 ? 1u : 0u);
+            for (int k = left_ > 0 ? left_ : 4; k < 4; ++k) {
+                q0 = q1;
+                q1 = q2;
+                q2 = q3;
+            }
         }
     }
-    if (lds_nodes > 0) {
-        const int base = g.off[lds_first];
-        for (int i = threadIdx.x; i < lds_nodes; i += blockDim.x) s_nodes[i] = g.nodes[base + i];
+    __device__ __attribute__((always_inline)) void need(int k, uint32_t a, uint32_t b, uint32_t stream, uint32_t k0,
+                                                        uint32_t k1)
+    {
+        if (left < k) {
+            block(a, b, stream, k0, k1, (draw & 3u) == 0u);
+            left = 4;
+        }
     }
-    __syncthreads();
-}
+    __device__ void skip(int k) { left = left < k ? 0 : left; }
+    __device__ float take()
+    {
+        const uint32_t v = q0;
+        q0 = q1; q1 = q2; q2 = q3;
+        --left;
+        return (float)(v >> 8) * 5.9604644775390625e-08f;
+    }
+    __device__ float take_exp1() { return neg_log_unit(1.0f - take()); }
+};
 
 // ---------------------------------------------------------------------------
 // Matrix-core fragments.  For v_mfma_f32_16x16x16_bf16, lane l (0..63) holds

@@ -164,17 +164,31 @@ hipError_t guide_forward(const nc_ctx *ctx, const nc_guide *gd, const float *X, 
                          float *H0, float *H1, float *H2);
 hipError_t guide_train_step(const nc_ctx *ctx, nc_guide *gd, const float *rec, int n, int rec_stride, float lr,
                             double *d_loss, bool apply);
+void launch_zero_u64(const nc_ctx *ctx, unsigned long long *p, int n);
 hipError_t launch_philox(const nc_ctx *ctx, const uint32_t *ctr, const uint32_t *key, uint32_t *out, int n);
 // Device memory a render launch writes before it starts: the job table, the
 // launch record (the renderer's rarely used parameters, at most kRareBytes)
 // and the 8 work-queue heads (128 words, 16 apart, zeroed by a kernel at each
 // launch).  Either the context's buffers or the no-allocation scratch.
 constexpr size_t kRareBytes = 1536;
+// The tail kernels (the last paths of a render
+// call): a wave hands its paths over when kTailLanes or fewer are left (twice as
+// many in a launch of hardly more than one path a lane), so a launch of 8192
+// waves (32 per CU) hands over kTailCap at most, each as kTailWords words at most
+// (42 MB per context).  kTailWaves waves (5 per SIMD, what the kernels' registers
+// allow) share them, 16 at a time.  Measured (505 k paths, ragged field / 65 k,
+// blob / 67 M, cumulus step, ms): 16 lanes 7.2 / 0.82 / 25.1, 32 lanes 7.4 and 6.3
+// (two clouds) / 0.69 / 26.0, 8 lanes 8.1 / 0.94 / 25.4.
+constexpr int kTailLanes = 16;
+constexpr uint32_t kTailCap = 8192 * 2 * kTailLanes;
+constexpr int kTailWords = 40;
+constexpr int kTailWaves = 5120;
 struct RenderScratch {
     JobView *jobs;
     unsigned long long *rare;
     unsigned long long *queue;   // 128 words per queue set
     int max_sets;                // queue sets it holds
+    uint32_t *tail = nullptr;    // kTailCap x kTailWords words for the paths of the tail kernel (null: no tail kernel)
 };
 hipError_t launch_render(const nc_ctx *ctx, const nc_grid *g, const float *d_kc, const OptView &op,
                          const JobView *jobs, int n_jobs, const nc_sampling &s, double *sum, double *sumsq,

@@ -602,54 +602,6 @@ hipError_t launch_transmittance(const nc_ctx *ctx, const nc_grid *g, const float
 // ===========================================================================
 
 
-enum LaneState { kIdle = 0, kPath = 1, kShadow = 2 };
-// Queue items a wave takes per global atomic: one per lane, so that the last
-// chunks are short (paths differ a lot in cost and the launch ends with the
-// slowest wave); 64 atomics per 64 x samples_per_item paths are cheap.
-constexpr int kChunk = 64;
-static_assert(kChunk >= 64, "a chunk must cover every lane of a wave that needs an item");
-
-__device__ inline void camera_ray(const CamView &c, int px, int py, float u1, float u2, float o[3], float d[3])
-{
-    if (c.type == 0) {
-        const float sx = (2.0f * ((float)px + u1) / (float)c.W - 1.0f) * c.sx;
-        const float sy = (1.0f - 2.0f * ((float)py + u2) / (float)c.H) * c.sy;
-        float v[3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            o[a] = c.pos[a];
-            v[a] = c.f[a] + sx * c.r[a] + sy * c.u[a];
-        }
-        const float inv = rsqrtf(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
-#pragma unroll
-        for (int a = 0; a < 3; ++a) d[a] = v[a] * inv;
-    } else {
-        const float sx = (((float)px + u1) / (float)c.W - 0.5f) * c.sx;
-        const float sy = (0.5f - ((float)py + u2) / (float)c.H) * c.sy;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            o[a] = c.pos[a] + sx * c.r[a] + sy * c.u[a];
-            d[a] = c.f[a];
-        }
-    }
-}
-
-// Lanes for which pred holds.  (The scalar count by hand: the compiler keeps
-// __popcll's result, and every comparison with it, in 64 bits, which the
-// scalar unit does not compare.)
-__device__ inline int lane_count(bool pred)
-{
-    const unsigned long long m = __ballot(pred);
-    int n;
-    asm("s_bcnt1_i32_b64 %0, %1" : "=s"(n) : "s"(m) : "scc");
-    return n;
-}
-
-__device__ inline unsigned int lanes_below(unsigned long long mask)
-{
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-}
-
 // Parameters of the renderer that only the sample, event and guide phases
 // need (the launch record).  They live in device memory; each workgroup
 // stages the ones its loop reads in LDS.
@@ -726,51 +678,21 @@ struct RenderArgs {
     int guide_lds;              // byte offset of the per-wave guide scratch in dynamic LDS
     float gpos[3];              // network position input: (x - lo) * gpos - 1 spans [-1, 1] over the box
     nc_counters *counters;
+    uint32_t *tail;             // paths handed to the tail kernel: word w of path i at [w tail_cap + i] (null: none are)
+    unsigned int *tail_count;
+    int tail_lanes;             // a wave hands its paths over when it has no more than these
+    uint32_t tail_cap;
     int n_sets;                 // guided mode: queue sets (described in the launch record)
     int lds_first, lds_nodes;
 };
 
-// Lane phases.  Each loop trip the wave runs the phase that the most lanes
-// are waiting in (ballot counts); the other lanes wait.  Expensive code
-// (events, ray starts, new samples) thus runs for many lanes at once instead
-// of diverging inside every traversal step.
-enum Phase { kPhCross = 0, kPhCollide = 1, kPhEvent = 2, kPhRay = 3, kPhSample = 4, kPhGuide = 5, kPhIdle = 6 };
 constexpr int kGuideMaxWait = 8;   // trips a partial tile of guided lanes may wait for more
-// Paths left in a wave, once the queues are drained, below which it runs every
-// phase in each trip.  505 k paths over a ragged field (a launch that is all
-// tail: its longest path scatters 2660 times): 13.8 ms with one phase a trip,
-// 11.9, 11.8 and 11.7 ms below 8, 16 and 64 lanes; 67 M paths lose from 64 (27.4
-// ms against 26.4 and 27.1: a wave still full of paths runs mostly empty phases).
-constexpr int kTailLanes = 16;
 enum RenderMode { kPlain = 0, kGuided = 1, kCollect = 2 };
 // ratio estimators: Russian roulette of a sun ray's estimate below this
 // transmissivity (survivors carry it).  On the cumulus view 0.25 reaches a
 // given image error soonest: 0.1 takes 1.6 % longer (more voxel crossings of
 // nearly spent sun rays), 0.5 takes 5 % longer (more variance).
 constexpr float kSunRoulette = 0.25f;
-static_assert(kPhGuide == 5 && kPhIdle == 6, "six running phases, one counter slot each");
-
-// After the optical thickness tau has been drawn or carried: a tentative
-// collision inside the current voxel, or a move to the next voxel.
-__device__ inline int voxel_phase(const Ray &r, float tau)
-{
-    return (r.khat > 0.0f && tau < r.khat * (r.texit - r.t)) ? kPhCollide : kPhCross;
-}
-
-// block-level event counters in LDS (same order as nc_counters)
-enum BlockCounter {
-    kCPaths = 0, kCSegments, kCTentative, kCNulls, kCReals, kCLeaf, kCGathers, kCReads, kCNee, kCTrunc,
-    kCTrips0, kCLanes0 = kCTrips0 + 6, kCCycles0 = kCLanes0 + 6, kCDeep = kCCycles0 + 6,
-    kNumBlockCounters = kCDeep + 1
-};
-
-__device__ inline void wave_count(unsigned long long *s_cnt, int k, bool pred)
-{
-    if (!s_cnt) return;   // no counters asked for
-    const unsigned long long m = __ballot(pred);
-    if (m && __lane_id() == 0) atomicAdd(s_cnt + k, (unsigned long long)__popcll(m));
-}
-
 __device__ inline void camera_ray_v(const CamView &c, int px, int py, float u1, float u2, float o[3],
                                     float d[3])
 {
@@ -1215,6 +1137,388 @@ hipError_t launch_guide_sample(const nc_ctx *ctx, const nc_guide *gd, const floa
     return hipGetLastError();
 }
 
+// Words of a path handed to the tail kernel.
+enum TailWord { kTwFlags = 0, kTwDraw = 1, kTwInts = 2, kTwFloats = 7, kTwAxes = 22, kTwEnd = 37 };
+static_assert(kTwEnd <= kTailWords, "a path fits its words");
+
+// A lane's path: its state, and the phases it goes through.  The renderer's
+// trips run a phase for the lanes waiting in it.
+//
+// The extended medium (kExt: a k-distribution, a tabulated phase function, the
+// solar disc) has its own variants; the others have none of it in their code,
+// so neither a register for a per-path gas extinction nor the table's search.
+template <int kMode, int kSun, bool kExt>
+struct PathState {
+    int phase = kPhSample;
+    int job = 0;                         // the lane's current view x sun
+    int pix = 0, s = 0;
+    float sun[3] = {0.0f, 0.0f, 1.0f};   // that job's sun direction (its irradiance is applied at the flush)
+    bool shadow = false;                 // the current ray is a sun ray
+    bool ground_ev = false;              // the current event is on the ground
+    bool start = false;                  // an event or sample of this trip starts a ray from r.o (along pd, or
+                                         // towards the sun)
+    int res = kContinue;                 // outcome of the last step (for the event phase)
+    float kc_hit = 0.0f;                 // k_c at the last real collision of a path ray; during a sun ray (ratio
+                                         // estimators) its transmissivity estimate so far
+    float acc = 0.0f, acc2 = 0.0f;       // the item's samples so far
+    float Lp = 0.0f;
+    float tau = 0.0f;
+    float pd[3] = {0.0f, 0.0f, 0.0f};    // path direction / direction of the next path ray
+    float w_nee = 0.0f;                  // sun contribution of the current event if its sun ray gets through
+    float p_cont = 0.0f;                 // probability that the path goes on after the event
+    int order = 0, segs = 0;
+    float beta = 1.0f;                   // path weight (guided mode)
+    float kev = 0.0f;                    // extinction at the current event (guided and collection modes)
+    float kg = 0.0f;                     // the path's gas extinction: a k-distribution point (kExt)
+    Ray r;                               // at an event, r.o holds its position (origin of the next ray)
+    RngBuf rng;
+    bool trunc = false, real = false, gathered = false, locate = false;   // outcomes of a step, for the statistics
+
+    __device__ float path_kg(const RenderArgs &A) const { return kExt ? kg : A.g.k_gas; }
+    // the next k random numbers come from one Philox block
+    __device__ __attribute__((always_inline)) void draws(const RenderArgs &A, int k)
+    {
+        rng.need(k, (uint32_t)pix, A.sample_base + (uint32_t)s, A.stream_base + (uint32_t)job, A.key0, A.key1);
+    }
+
+    __device__ __attribute__((always_inline)) void event(const RenderArgs &A, const RareShared &s_rare)
+    {
+#define NC_R(f) lds_get(s_rare.f)
+        float &t_sun = kc_hit;
+        const HGc hg{NC_R(hg.a), NC_R(hg.b), NC_R(hg.c), NC_R(hg.e), NC_R(hg.d), NC_R(hg.r2g)};
+        const int max_scatter = NC_R(max_scatter);
+        // three numbers cover an event (absorption, then two for the new
+        // direction); a guided step takes absorption plus three.  Lanes
+        // that go on to their sun ray first use none of them: theirs come
+        // with the ray's, below
+        constexpr int kEventDraws = kMode == kGuided ? 4 : 3;
+        if (kExt && A.op.cone) draws(A, kEventDraws);
+        bool cont = false;               // go on to the scatter / reflect decision
+        if (shadow) {
+            if (res == kExit) Lp += beta * w_nee * (kSun != 0 ? t_sun : 1.0f);   // the sun ray got through
+            cont = true;
+        } else if (res == kReal) {
+            // volume event: local estimate of the sun, then scatter or absorb
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                pd[a] = r.d[a];
+                r.o[a] = r.o[a] + r.t * r.d[a];
+            }
+            const float kd = kc_hit;
+            kev = kd + path_kg(A);
+            const float ssa = NC_R(ssa) * kd * __builtin_amdgcn_rcpf(kd + path_kg(A));
+            float gain = 1.0f;
+            if (kExt && A.op.cone) {
+                // solar disc: the local estimate's direction drawn in its cone
+                const JobView &J = NC_R(jobs)[job];
+                const float s0[3] = {J.sun[0], J.sun[1], J.sun[2]};
+                const float c1 = rng.take(), c2 = rng.take();
+                float w[3];
+                cone_dir(s0, A.op.cone_cos, c1, c2, w);
+                sun[0] = w[0];
+                sun[1] = w[1];
+                sun[2] = w[2];
+                gain = A.op.cone_gain;
+            }
+            const float mu = pd[0] * sun[0] + pd[1] * sun[1] + pd[2] * sun[2];
+            w_nee = ssa * (kExt ? phase_eval(hg, A.op.tab, mu) : hg_phase(hg, mu)) * gain;
+            p_cont = ssa;
+            ground_ev = false;
+            ++order;
+            if (max_scatter >= 0 && order > max_scatter) {
+                phase = kPhSample;
+            } else if (w_nee > 0.0f) {
+                shadow = true;
+                start = true;
+            } else {
+                cont = true;
+            }
+        } else if (r.d[2] < 0.0f) {
+            // ground hit: Lambertian local estimate
+            const float tg = -r.o[2] * __builtin_amdgcn_rcpf(r.d[2]);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) pd[a] = r.d[a];
+            r.o[0] = r.o[0] + tg * r.d[0];
+            r.o[1] = r.o[1] + tg * r.d[1];
+            r.o[2] = 0.0f;
+            const float rho = NC_R(jobs)[job].rho;
+            float gain = 1.0f;
+            if (kExt && A.op.cone) {
+                const JobView &J = NC_R(jobs)[job];
+                const float s0[3] = {J.sun[0], J.sun[1], J.sun[2]};
+                const float c1 = rng.take(), c2 = rng.take();
+                float w[3];
+                cone_dir(s0, A.op.cone_cos, c1, c2, w);
+                sun[0] = w[0];
+                sun[1] = w[1];
+                sun[2] = w[2];
+                gain = A.op.cone_gain;
+            }
+            w_nee = rho * (1.0f / kPi) * sun[2] * gain;   // <= 0 (no sun ray) when the direction is below the horizon
+            p_cont = rho;
+            ground_ev = true;
+            ++order;
+            if (max_scatter >= 0 && order > max_scatter) {
+                phase = kPhSample;
+            } else if (w_nee > 0.0f) {
+                shadow = true;
+                start = true;
+            } else {
+                cont = true;
+            }
+        } else {
+            // escaped upward: a camera ray that met nothing may look into the solar disc
+            if (kExt && A.op.cone && order == 0 && !ground_ev) {
+                const JobView &J = NC_R(jobs)[job];
+                if (r.d[0] * J.sun[0] + r.d[1] * J.sun[1] + r.d[2] * J.sun[2] >= A.op.cone_cos)
+                    Lp += beta * A.op.cone_L;
+            }
+            phase = kPhSample;
+        }
+        if (!cont) {
+            if (!(kExt && A.op.cone)) rng.skip(kEventDraws);
+        } else {
+            shadow = false;
+            // (the disc's draw may have left too few numbers for the scattering)
+            draws(A, kEventDraws);
+            if (max_scatter >= 0 && order >= max_scatter) {
+                phase = kPhSample;
+            } else if (rng.take() >= p_cont) {
+                phase = kPhSample;       // absorbed (volume) or not reflected (ground)
+            } else if (kMode == kGuided && !ground_ev &&
+                       (A.guide_max_order == 0 || order <= A.guide_max_order)) {
+                phase = kPhGuide;        // the network proposes the new direction (a later trip)
+            } else {
+                const float u1 = rng.take(), u2 = rng.take();
+                const float win[3] = {pd[0], pd[1], pd[2]};
+                if (ground_ev)
+                    lambert(pd, u1, u2);
+                else
+                    turn(pd, kExt ? phase_sample_mu(hg, A.op.tab, u1) : hg_sample_mu(hg, u1), u2);
+                start = true;
+                if (kMode == kCollect && !ground_ev) {
+                    // training record: vertex, incoming and outgoing directions, radiance so far
+                    const unsigned long long k = atomicAdd(A.col.count, 1ull);
+                    if (k < A.col.cap) {
+                        float *q = A.col.records + k * kGuideRecord;
+#pragma unroll
+                        for (int a = 0; a < 3; ++a) {
+                            q[a] = (r.o[a] - A.g.lo[a]) * A.gpos[a] - 1.0f;
+                            q[3 + a] = win[a];
+                            q[7 + a] = pd[a];
+                        }
+                        q[6] = __logf(1.0f + kev);
+                        q[10] = Lp;
+                        q[11] = __uint_as_float((uint32_t)(pix * A.col_spp + s));
+                    }
+                }
+            }
+        }
+    }
+
+#undef NC_R
+
+    __device__ __attribute__((always_inline)) void ray_start(const RenderArgs &A)
+    {
+        float &t_sun = kc_hit;
+        draws(A, 1);
+        const float o[3] = {r.o[0], r.o[1], r.o[2]};
+        const float rd[3] = {shadow ? sun[0] : pd[0], shadow ? sun[1] : pd[1], shadow ? sun[2] : pd[2]};
+        phase = kPhRay;
+        if (!ray_setup(A.g, r, o, rd, 0.0f)) {
+            // misses the box: the next step finds the ray outside
+            r.t = r.tend = r.texit = 0.0f;
+            r.khat = 0.0f;
+            r.kmin = 0.0f;
+            r.lev = A.g.L;
+            phase = kPhCross;
+        }
+        if (kSun != 0 && shadow) t_sun = 1.0f;
+        tau = rng.take_exp1();
+    }
+
+    // an end of the ray (and, with roulette, of a spent sun ray) or the next voxel
+    __device__ __attribute__((always_inline)) void voxel_step(const RenderArgs &A, const NodeSrc &ns)
+    {
+        float &t_sun = kc_hit;
+        const bool crossing = phase == kPhCross;
+        locate = !crossing;
+        if (crossing) {
+            const float dt = r.texit - r.t;
+            tau -= r.khat * dt;
+            const bool resid = kSun == 2 && shadow;
+            if (resid) {
+                t_sun *= __expf(-(r.kmin + path_kg(A)) * dt);
+                if (t_sun < kSunRoulette) {     // Russian roulette on small estimates
+                    draws(A, 1);
+                    t_sun = rng.take() * kSunRoulette < t_sun ? kSunRoulette : 0.0f;
+                }
+            }
+            // the ray ends here when its estimate is zero or it leaves the box
+            const bool spent = resid && t_sun == 0.0f;
+            res = spent ? kReal : kExit;
+            const bool inside = step_cell(A.g, r);
+            locate = inside && !spent;
+            phase = locate ? phase : kPhEvent;
+        }
+        if (locate) {
+            uint32_t nr = 0;   // (counted by ballot when statistics are on)
+            locate_voxel<true>(A.g, ns, r, A.op.mscale, nr);
+            leaf_exit(A.g, r);
+            if (kSun == 2 && shadow) r.khat = fmaxf(r.khat - (r.kmin + path_kg(A)), 0.0f);
+            phase = voxel_phase(r, tau);
+            if (crossing && ++segs >= A.op.max_segments) {
+                trunc = true;
+                phase = kPhSample;      // stop the path
+            }
+        }
+    }
+
+    // a tentative collision in the current voxel: real or null
+    // (k_at(): k_c of the cell at r.t)
+    template <class Gather>
+    __device__ __attribute__((always_inline)) void collision(const RenderArgs &A, Gather k_at)
+    {
+        float &t_sun = kc_hit;
+        draws(A, 2);
+        const float t0 = r.t;
+        r.t = fminf(r.t + tau * __builtin_amdgcn_rcpf(r.khat), r.texit);
+        const float u = rng.take();
+        const float thr = u * r.khat;
+        const float kmin = r.kmin + path_kg(A);
+        // a sun ray by delta tracking is stopped below the voxel's minimum
+        // without reading k; a level-0 voxel is one cell: k is known
+        const bool below = kSun == 0 && shadow && thr < kmin;
+        float kx = r.kmin;
+        gathered = (r.lev != 0) & !below;
+        if (gathered) kx = k_at();
+        if (kSun != 0 && shadow) {
+            // ratio tracking (control 0) or residual ratio tracking (control
+            // = the voxel minimum; r.khat then holds the residual majorant):
+            // every tentative collision scales the estimate t_sun by
+            // 1 - (k - k_ctrl) / khat, the control part by exp(-k_ctrl dt)
+            const float kctrl = kSun == 2 ? kmin : 0.0f;
+            t_sun *= __expf(-kctrl * (r.t - t0)) *
+                     fmaxf(0.0f, 1.0f - (kx + path_kg(A) - kctrl) * __builtin_amdgcn_rcpf(r.khat));
+            if (t_sun < kSunRoulette)       // Russian roulette on small estimates
+                t_sun = u * kSunRoulette < t_sun ? kSunRoulette : 0.0f;
+            real = t_sun == 0.0f;
+        } else {
+            if (!below) kc_hit = kx;
+            real = below | (thr < kx + path_kg(A));
+        }
+        if (real) {
+            res = kReal;
+            phase = kPhEvent;
+        } else {
+            tau = rng.take_exp1();
+            phase = voxel_phase(r, tau);
+            if (++segs >= A.op.max_segments) {
+                trunc = true;
+                phase = kPhSample;
+            }
+        }
+    }
+
+    // Hand the path to the tail kernel: its words (TailWord's order) at p, p + stride, ...
+    __device__ __attribute__((always_inline)) void hand_over(uint32_t *p, size_t stride) const
+    {
+        auto put = [&](uint32_t v) {
+            *p = v;
+            p += stride;
+        };
+        // (before a path's first voxel its mask and level hold anything: masked)
+        put((uint32_t)(phase | (shadow ? 8 : 0) | (ground_ev ? 16 : 0) | (res << 5) | ((r.xmask & 7) << 8) |
+                       ((r.lev & 0xff) << 12) | (rng.left << 20)));
+        put(rng.draw);
+        put((uint32_t)job);
+        put((uint32_t)pix);
+        put((uint32_t)s);
+        put((uint32_t)order);
+        put((uint32_t)segs);
+        const float f[] = {acc, acc2, Lp, tau, kc_hit, w_nee, p_cont, r.t, r.tend, r.texit, r.khat, r.kmin, beta, kev, kg};
+#pragma unroll
+        for (int k = 0; k < 15; ++k) put(__float_as_uint(f[k]));
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            put(__float_as_uint(r.o[a]));
+            put(__float_as_uint(r.d[a]));
+            put(__float_as_uint(pd[a]));
+            put(__float_as_uint(sun[a]));
+            // a ray's first cell, later the cell past its voxel: only one of them is live
+            put((uint32_t)(phase == kPhRay ? r.c[a] : r.cn[a]));
+        }
+    }
+};
+
+// The network phase of a wave: inference on the matrix cores, then the MIS step
+// in the same layout, for the first `best` lanes (by rank) that wait for it, in
+// tiles of 16.  gb: the workgroup's network in LDS.  The whole wave calls it.
+template <bool kExt, class Path>
+__device__ __attribute__((always_inline)) inline void guide_step(Path &P, const RenderArgs &A,
+                                                                 const RareShared &s_rare, char *gb, int best)
+{
+#define NC_R(f) lds_get(s_rare.f)
+    const int lane = __lane_id();
+    // ---- guided scattering: network inference on the matrix cores,
+    // then the MIS step in the same layout.  The first `best` waiting
+    // lanes (by rank) are packed into tiles of 16.
+    const bool waiting = P.phase == kPhGuide;
+    const unsigned long long want = __ballot(waiting);
+    const int rank = __popcll(want & ((1ull << lane) - 1ull));
+    const bool active = waiting && rank < best;
+    const short *wl = reinterpret_cast<const short *>(gb);
+    const float *bl = reinterpret_cast<const float *>(gb + kWOff[4] * 2);
+    char *wt = gb + kGuideWeightBytes + (threadIdx.x >> 6) * kGuideScratchPerWave;
+    short *tin = reinterpret_cast<short *>(wt);
+    float *tf = reinterpret_cast<float *>(wt + kGuideInBytes);
+    const int ntiles = (best + 15) >> 4;
+    const int row = rank & 15, col = __lane_id() & 15, kq = lane >> 4;
+    for (int t = 0; t < ntiles; ++t) {
+        const bool owner = active && (rank >> 4) == t;
+        if (owner) {
+            float x[7];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                x[a] = (P.r.o[a] - A.g.lo[a]) * A.gpos[a] - 1.0f;
+                x[3 + a] = P.pd[a];
+            }
+            x[6] = __logf(1.0f + P.kev);
+            put_guide_inputs(tin + row * 16, x);
+            // the event trip left three numbers for this step
+            float *f = tf + row * 8;
+            const float u_sel = P.rng.take();
+            f[0] = P.pd[0];
+            f[1] = P.pd[1];
+            f[2] = P.pd[2];
+            f[3] = u_sel;
+            f[4] = lobe_uniform(u_sel, A.guide_frac);
+            f[5] = P.rng.take();   // u1
+            f[6] = P.rng.take();   // u2
+        }
+        wave_sync();
+        float z[12];
+        guide_tile_forward(wl, bl, tin, lane, z);
+        const GuidedStep st = guided_turn_tile<kExt>(z, tf + col * 8, A.guide_frac,
+                                                        HGc{NC_R(hg.a), NC_R(hg.b), NC_R(hg.c), NC_R(hg.e),
+                                                            NC_R(hg.d), NC_R(hg.r2g)},
+                                                        A.op.tab, kq);
+        // each owner takes its column's result
+        const int src = owner ? row : lane;
+        const float d0 = __shfl(st.d[0], src), d1 = __shfl(st.d[1], src), d2 = __shfl(st.d[2], src);
+        const float wf = __shfl(st.w, src);
+        if (owner) {
+            P.pd[0] = d0;
+            P.pd[1] = d1;
+            P.pd[2] = d2;
+            P.beta *= wf;
+            P.start = true;
+        }
+        wave_sync();
+    }
+#undef NC_R
+}
+
 // kSets: the guided batch with more than one network (queue set); a
 // workgroup whose set has drained moves to another.  Compiled only where a
 // launch has several sets: the loop around the tracing loop keeps many more
@@ -1257,35 +1561,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
     // statistics (ballots, LDS atomics, clock reads) only when counters are asked for
     const bool stats = A.counters != nullptr;
     unsigned long long *const cnt = stats ? s_cnt : nullptr;
-    int job = 0;                           // the lane's current view x sun
-    float sun[3] = {0.0f, 0.0f, 1.0f};     // that job's sun direction (its irradiance is applied at the flush)
-
-    int phase = kPhSample;
-    bool shadow = false;       // the current ray is a sun ray
+    PathState<kMode, kSun, kExt> P;
+    P.rng.reset();
+    P.kg = g.k_gas;
+    int &phase = P.phase, &job = P.job, &pix = P.pix, &s = P.s;
+    float(&sun)[3] = P.sun, (&pd)[3] = P.pd;
+    float &acc = P.acc, &acc2 = P.acc2, &Lp = P.Lp, &beta = P.beta, &kg = P.kg, &w_nee = P.w_nee, &p_cont = P.p_cont;
+    bool &shadow = P.shadow, &ground_ev = P.ground_ev, &start = P.start;
+    Ray &r = P.r;
+    RngBuf &rng = P.rng;
     bool have_item = false;    // the lane holds a queue item with samples left
     bool traced = false;       // a path has been traced since the last sample phase
-    int res = kContinue;       // outcome of the last step (for the event phase)
-    float kc_hit = 0.0f;       // k_c at the last real collision of a path ray
-    float &t_sun = kc_hit;     // during a sun ray (ratio estimators): its transmissivity estimate so far
-    int pix = 0, s = 0, s_end = 0;
-    float acc = 0.0f, acc2 = 0.0f;
-    float Lp = 0.0f;
-    Ray r;                     // at an event, r.o holds the event position (origin of the next ray)
-    float tau = 0.0f;
-    RngBuf rng;
-    rng.reset();
-    float pd[3] = {0, 0, 0};   // path direction / direction of the next path ray
-    float w_nee = 0.0f;        // sun contribution of the current event if its sun ray gets through
-    float p_cont = 0.0f;       // probability that the path goes on after the event
-    bool ground_ev = false;
-    int order = 0, segs = 0;
-    float beta = 1.0f;                   // path weight (guided mode)
-    float kev = 0.0f;                    // extinction at the current event (guided and collection modes)
-    float kg = g.k_gas;                  // the path's gas extinction: a k-distribution point (kExt)
-    // kExt: the extended medium (a k-distribution, a tabulated phase function,
-    // the solar disc); the other variants have none of them in their code, so
-    // neither a register for a per-path gas extinction nor the table's search
-    auto path_kg = [&]() { return kExt ? kg : g.k_gas; };
+    int s_end = 0;
     unsigned long long chunk_base = 0;   // wave-uniform: the wave's chunk of queue items
     int chunk_left = 0;
     bool queue_done = false;
@@ -1310,10 +1597,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
         const int n_guide = kMode == kGuided ? lane_count(phase == kPhGuide) : 0;
         const int n_other = n_step + n_coll + n_event + n_sample;
         if (n_other + n_guide == 0) break;
+        if (kMode != kGuided && A.tail && queue_done && n_other <= A.tail_lanes) {
+            // Once the queues are drained and few paths are left in the wave, they
+            // go to the tail kernel (unless a lane has further samples to start)
+            const bool going = phase < kPhSample;
+            const unsigned long long m = __ballot(going);
+            if (m && !__ballot(going && s + 1 < s_end)) {
+                unsigned int base = 0;
+                if (lane == 0) base = atomicAdd(A.tail_count, (unsigned int)__popcll(m));
+                base = __shfl(base, 0);
+                if (going) {
+                    P.hand_over(A.tail + base + lanes_below(m), A.tail_cap);
+                    phase = kPhIdle;
+                }
+                continue;
+            }
+        }
         int run = kPhCross, best = n_step;
         if (n_coll >= best) { run = kPhCollide; best = n_coll; }
         if (n_event >= best) { run = kPhEvent; best = n_event; }
-        if (n_sample > best) { run = kPhSample; best = n_sample; }
+        // (a lane between paths waits for no one else's trip: counted twice, 67 M
+        // paths over cumulus fields 2 % faster, single views up to 5 %; weights of
+        // 0.75 to 2 on the other phases changed nothing by more than 2 %)
+        if (2 * n_sample > best) { run = kPhSample; best = n_sample; }
         if (kMode == kGuided && n_guide > 0) {
             // lanes waiting for the network run as full tiles of 16, once two
             // tiles' worth wait (the phase's set-up is then shared by at least
@@ -1329,11 +1635,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
                 ++guide_wait;
             }
         }
-        // Once the queues are drained the launch ends with the longest paths left,
-        // and a wave with few of them runs every phase in one trip, in the order
-        // a path goes through them: each lane then advances at every trip
-        // instead of waiting for its phase's turn.
-        const bool all = queue_done && n_other + n_guide <= kTailLanes;
+        // a guided wave with few paths runs every phase in one trip instead, in the
+        // order a path goes through them: each lane then advances at every trip
+        const bool all = kMode == kGuided && queue_done && n_other + n_guide <= kTailLanes;
         const bool run_step = all || run == kPhCross, run_coll = all || run == kPhCollide;
         const bool run_event = all || run == kPhEvent, run_sample = run == kPhSample || (all && n_sample > 0);
         const bool run_guide = run == kPhGuide;
@@ -1351,7 +1655,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
         auto trip_end = [&](int ph) {
             if (stats && lane == 0) atomicAdd(s_cnt + kCCycles0 + ph, (unsigned long long)(wall_clock64() - t_trip));
         };
-        bool start = false;   // the lane starts a ray at the end of this trip (along pd, or towards the sun)
+        start = false;
 
         if (run_sample) {
             trip_begin(kPhSample, phase == kPhSample);
@@ -1464,8 +1768,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
                 const JobView &J = NC_R(jobs)[job];
                 const int W = J.cam.W;
                 const int py = pix / W, px = pix - py * W;
-                rng.need(kExt && A.op.kd_n ? 3 : 2, (uint32_t)pix, A.sample_base + (uint32_t)s, A.stream_base + (uint32_t)job, A.key0,
-                         A.key1);
+                P.draws(A, kExt && A.op.kd_n ? 3 : 2);
                 if (kExt && A.op.kd_n) {
                     // spectral integration: the path's quadrature point (Section 4.1)
                     // (unrolled over the table, so that its entries stay scalar kernel arguments)
@@ -1486,8 +1789,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
                 for (int a = 0; a < 3; ++a) r.o[a] = o[a];
                 Lp = 0.0f;
                 beta = 1.0f;
-                order = 0;
-                segs = 0;
+                P.order = 0;
+                P.segs = 0;
                 shadow = false;
                 traced = true;
                 start = true;
@@ -1500,8 +1803,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
                     if (kExt && A.op.cone) {
                         // the direct beam along a direction drawn in the disc's cone
                         const float s0[3] = {sun[0], sun[1], sun[2]};
-                        rng.need(2, (uint32_t)pix, A.sample_base + (uint32_t)s, A.stream_base + (uint32_t)job, A.key0,
-                                 A.key1);
+                        P.draws(A, 2);
                         const float c1 = rng.take(), c2 = rng.take();
                         float w[3];
                         cone_dir(s0, A.op.cone_cos, c1, c2, w);
@@ -1520,199 +1822,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
         }
         if (run_event) {
             trip_begin(kPhEvent, phase == kPhEvent);
-            if (phase == kPhEvent) {
-                const HGc hg{NC_R(hg.a), NC_R(hg.b), NC_R(hg.c), NC_R(hg.e), NC_R(hg.d), NC_R(hg.r2g)};
-                const int max_scatter = NC_R(max_scatter);
-                // three numbers cover an event (absorption, then two for the new
-                // direction); a guided step takes absorption plus three.  Lanes
-                // that go on to their sun ray first use none of them: theirs come
-                // with the ray's, below
-                constexpr int kEventDraws = kMode == kGuided ? 4 : 3;
-                if (kExt && A.op.cone) rng.need(kEventDraws, (uint32_t)pix, A.sample_base + (uint32_t)s, A.stream_base + (uint32_t)job, A.key0, A.key1);
-                bool cont = false;               // go on to the scatter / reflect decision
-                if (shadow) {
-                    if (res == kExit) Lp += beta * w_nee * (kSun != 0 ? t_sun : 1.0f);   // the sun ray got through
-                    cont = true;
-                } else if (res == kReal) {
-                    // volume event: local estimate of the sun, then scatter or absorb
-#pragma unroll
-                    for (int a = 0; a < 3; ++a) {
-                        pd[a] = r.d[a];
-                        r.o[a] = r.o[a] + r.t * r.d[a];
-                    }
-                    const float kd = kc_hit;
-                    kev = kd + path_kg();
-                    const float ssa = NC_R(ssa) * kd * __builtin_amdgcn_rcpf(kd + path_kg());
-                    float gain = 1.0f;
-                    if (kExt && A.op.cone) {
-                        // solar disc: the local estimate's direction drawn in its cone
-                        const JobView &J = NC_R(jobs)[job];
-                        const float s0[3] = {J.sun[0], J.sun[1], J.sun[2]};
-                        const float c1 = rng.take(), c2 = rng.take();
-                        float w[3];
-                        cone_dir(s0, A.op.cone_cos, c1, c2, w);
-                        sun[0] = w[0];
-                        sun[1] = w[1];
-                        sun[2] = w[2];
-                        gain = A.op.cone_gain;
-                    }
-                    const float mu = pd[0] * sun[0] + pd[1] * sun[1] + pd[2] * sun[2];
-                    w_nee = ssa * (kExt ? phase_eval(hg, A.op.tab, mu) : hg_phase(hg, mu)) * gain;
-                    p_cont = ssa;
-                    ground_ev = false;
-                    ++order;
-                    if (max_scatter >= 0 && order > max_scatter) {
-                        phase = kPhSample;
-                    } else if (w_nee > 0.0f) {
-                        shadow = true;
-                        start = true;
-                    } else {
-                        cont = true;
-                    }
-                } else if (r.d[2] < 0.0f) {
-                    // ground hit: Lambertian local estimate
-                    const float tg = -r.o[2] * __builtin_amdgcn_rcpf(r.d[2]);
-#pragma unroll
-                    for (int a = 0; a < 3; ++a) pd[a] = r.d[a];
-                    r.o[0] = r.o[0] + tg * r.d[0];
-                    r.o[1] = r.o[1] + tg * r.d[1];
-                    r.o[2] = 0.0f;
-                    const float rho = NC_R(jobs)[job].rho;
-                    float gain = 1.0f;
-                    if (kExt && A.op.cone) {
-                        const JobView &J = NC_R(jobs)[job];
-                        const float s0[3] = {J.sun[0], J.sun[1], J.sun[2]};
-                        const float c1 = rng.take(), c2 = rng.take();
-                        float w[3];
-                        cone_dir(s0, A.op.cone_cos, c1, c2, w);
-                        sun[0] = w[0];
-                        sun[1] = w[1];
-                        sun[2] = w[2];
-                        gain = A.op.cone_gain;
-                    }
-                    w_nee = rho * (1.0f / kPi) * sun[2] * gain;   // <= 0 (no sun ray) when the direction is below the horizon
-                    p_cont = rho;
-                    ground_ev = true;
-                    ++order;
-                    if (max_scatter >= 0 && order > max_scatter) {
-                        phase = kPhSample;
-                    } else if (w_nee > 0.0f) {
-                        shadow = true;
-                        start = true;
-                    } else {
-                        cont = true;
-                    }
-                } else {
-                    // escaped upward: a camera ray that met nothing may look into the solar disc
-                    if (kExt && A.op.cone && order == 0 && !ground_ev) {
-                        const JobView &J = NC_R(jobs)[job];
-                        if (r.d[0] * J.sun[0] + r.d[1] * J.sun[1] + r.d[2] * J.sun[2] >= A.op.cone_cos)
-                            Lp += beta * A.op.cone_L;
-                    }
-                    phase = kPhSample;
-                }
-                if (!cont) {
-                    if (!(kExt && A.op.cone)) rng.skip(kEventDraws);
-                } else {
-                    shadow = false;
-                    // (the disc's draw may have left too few numbers for the scattering)
-                    rng.need(kEventDraws, (uint32_t)pix, A.sample_base + (uint32_t)s, A.stream_base + (uint32_t)job, A.key0, A.key1);
-                    if (max_scatter >= 0 && order >= max_scatter) {
-                        phase = kPhSample;
-                    } else if (rng.take() >= p_cont) {
-                        phase = kPhSample;       // absorbed (volume) or not reflected (ground)
-                    } else if (kMode == kGuided && !ground_ev &&
-                               (A.guide_max_order == 0 || order <= A.guide_max_order)) {
-                        phase = kPhGuide;        // the network proposes the new direction (a later trip)
-                    } else {
-                        const float u1 = rng.take(), u2 = rng.take();
-                        const float win[3] = {pd[0], pd[1], pd[2]};
-                        if (ground_ev)
-                            lambert(pd, u1, u2);
-                        else
-                            turn(pd, kExt ? phase_sample_mu(hg, A.op.tab, u1) : hg_sample_mu(hg, u1), u2);
-                        start = true;
-                        if (kMode == kCollect && !ground_ev) {
-                            // training record: vertex, incoming and outgoing directions, radiance so far
-                            const unsigned long long k = atomicAdd(A.col.count, 1ull);
-                            if (k < A.col.cap) {
-                                float *q = A.col.records + k * kGuideRecord;
-#pragma unroll
-                                for (int a = 0; a < 3; ++a) {
-                                    q[a] = (r.o[a] - g.lo[a]) * A.gpos[a] - 1.0f;
-                                    q[3 + a] = win[a];
-                                    q[7 + a] = pd[a];
-                                }
-                                q[6] = __logf(1.0f + kev);
-                                q[10] = Lp;
-                                q[11] = __uint_as_float((uint32_t)(pix * A.col_spp + s));
-                            }
-                        }
-                    }
-                }
-            }
+            if (phase == kPhEvent)
+                P.event(A, s_rare);
             trip_end(kPhEvent);
         }
         if (kMode == kGuided && run_guide) {
             trip_begin(kPhGuide, phase == kPhGuide);
-            // ---- guided scattering: network inference on the matrix cores,
-            // then the MIS step in the same layout.  The first `best` waiting
-            // lanes (by rank) are packed into tiles of 16.
-            const bool waiting = phase == kPhGuide;
-            const unsigned long long want = __ballot(waiting);
-            const int rank = __popcll(want & ((1ull << lane) - 1ull));
-            const bool active = waiting && rank < best;
             extern __shared__ __align__(16) float2 s_dyn[];
-            char *gb = reinterpret_cast<char *>(s_dyn) + A.guide_lds;
-            const short *wl = reinterpret_cast<const short *>(gb);
-            const float *bl = reinterpret_cast<const float *>(gb + kWOff[4] * 2);
-            char *wt = gb + kGuideWeightBytes + (threadIdx.x >> 6) * kGuideScratchPerWave;
-            short *tin = reinterpret_cast<short *>(wt);
-            float *tf = reinterpret_cast<float *>(wt + kGuideInBytes);
-            const int ntiles = (best + 15) >> 4;
-            const int row = rank & 15, col = lane & 15, kq = lane >> 4;
-            for (int t = 0; t < ntiles; ++t) {
-                const bool owner = active && (rank >> 4) == t;
-                if (owner) {
-                    float x[7];
-#pragma unroll
-                    for (int a = 0; a < 3; ++a) {
-                        x[a] = (r.o[a] - g.lo[a]) * A.gpos[a] - 1.0f;
-                        x[3 + a] = pd[a];
-                    }
-                    x[6] = __logf(1.0f + kev);
-                    put_guide_inputs(tin + row * 16, x);
-                    // the event trip left three numbers for this step
-                    float *f = tf + row * 8;
-                    const float u_sel = rng.take();
-                    f[0] = pd[0];
-                    f[1] = pd[1];
-                    f[2] = pd[2];
-                    f[3] = u_sel;
-                    f[4] = lobe_uniform(u_sel, A.guide_frac);
-                    f[5] = rng.take();   // u1
-                    f[6] = rng.take();   // u2
-                }
-                wave_sync();
-                float z[12];
-                guide_tile_forward(wl, bl, tin, lane, z);
-                const GuidedStep st = guided_turn_tile<kExt>(z, tf + col * 8, A.guide_frac,
-                                                                HGc{NC_R(hg.a), NC_R(hg.b), NC_R(hg.c), NC_R(hg.e),
-                                                                    NC_R(hg.d), NC_R(hg.r2g)},
-                                                                A.op.tab, kq);
-                // each owner takes its column's result
-                const int src = owner ? row : lane;
-                const float d0 = __shfl(st.d[0], src), d1 = __shfl(st.d[1], src), d2 = __shfl(st.d[2], src);
-                const float wf = __shfl(st.w, src);
-                if (owner) {
-                    pd[0] = d0;
-                    pd[1] = d1;
-                    pd[2] = d2;
-                    beta *= wf;
-                    start = true;
-                }
-                wave_sync();
-            }
+            guide_step<kExt>(P, A, s_rare, reinterpret_cast<char *>(s_dyn) + A.guide_lds, best);
             trip_end(kPhGuide);
         }
         if (run_sample || run_event || run_guide) {
@@ -1720,22 +1837,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
             // here 20 lanes set theirs up at once; at the top of a step trip, where
             // only the rays of one earlier trip wait, it was 7
             if (stats) wave_count(cnt, kCNee, start && shadow);
-            if (start) {
-                rng.need(1, (uint32_t)pix, A.sample_base + (uint32_t)s, A.stream_base + (uint32_t)job, A.key0, A.key1);
-                const float o[3] = {r.o[0], r.o[1], r.o[2]};
-                const float rd[3] = {shadow ? sun[0] : pd[0], shadow ? sun[1] : pd[1], shadow ? sun[2] : pd[2]};
-                phase = kPhRay;
-                if (!ray_setup(g, r, o, rd, 0.0f)) {
-                    // misses the box: the next step finds the ray outside
-                    r.t = r.tend = r.texit = 0.0f;
-                    r.khat = 0.0f;
-                    r.kmin = 0.0f;
-                    r.lev = g.L;
-                    phase = kPhCross;
-                }
-                if (kSun != 0 && shadow) t_sun = 1.0f;
-                tau = rng.take_exp1();
-            }
+            if (start) P.ray_start(A);
         }
         if (run_step) {
             trip_begin(kPhCross, (phase == kPhCross) | (phase == kPhRay));
@@ -1744,47 +1846,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
             // cell of a new ray share the location of the voxel (ancestry mask,
             // node) and its exit
             const bool crossing = phase == kPhCross;
-            const bool resid = crossing && shadow && kSun == 2;
-            bool locate = phase == kPhRay, trunc = false;
-            const bool hit = locate;
-            if (crossing) {
-                const float dt = r.texit - r.t;
-                tau -= r.khat * dt;
-                if (resid) {
-                    t_sun *= __expf(-(r.kmin + path_kg()) * dt);
-                    if (t_sun < kSunRoulette) {     // Russian roulette on small estimates
-                        rng.need(1, (uint32_t)pix, A.sample_base + (uint32_t)s, A.stream_base + (uint32_t)job, A.key0, A.key1);
-                        t_sun = rng.take() * kSunRoulette < t_sun ? kSunRoulette : 0.0f;
-                    }
-                }
-                // the ray ends here when its estimate is zero or it leaves the box
-                const bool spent = resid && t_sun == 0.0f;
-                res = spent ? kReal : kExit;
-                const bool inside = step_cell(g, r);
-                locate = inside && !spent;
-                phase = locate ? phase : kPhEvent;
-            }
-            if (locate) {
-                uint32_t nr = 0;   // (counted by ballot below when statistics are on)
-                locate_voxel<true>(g, ns, r, A.op.mscale, nr);
-                leaf_exit(g, r);
-                if (kSun == 2 && shadow) r.khat = fmaxf(r.khat - (r.kmin + path_kg()), 0.0f);
-                phase = voxel_phase(r, tau);
-                if (crossing && ++segs >= A.op.max_segments) {
-                    trunc = true;
-                    phase = kPhSample;      // stop the path
-                }
-            }
+            P.locate = P.trunc = false;
+            if (crossing | (phase == kPhRay)) P.voxel_step(A, ns);
             if (stats) {
                 // memory reads of a voxel lookup: the cell, the ancestry mask, and the
                 // node when its level is not staged in LDS
-                wave_count(cnt, kCReads, locate);
-                if (g.L >= 1) wave_count(cnt, kCReads, locate);
-                wave_count(cnt, kCReads, locate && r.lev >= 1 && r.lev < ns.lds_first);
+                wave_count(cnt, kCReads, P.locate);
+                if (g.L >= 1) wave_count(cnt, kCReads, P.locate);
+                wave_count(cnt, kCReads, P.locate && r.lev >= 1 && r.lev < ns.lds_first);
                 wave_count(cnt, kCSegments, crossing);
-                wave_count(cnt, kCLeaf, locate);
-                wave_count(cnt, kCDeep, locate && r.lev < ns.lds_first);
-                wave_count(cnt, kCTrunc, trunc);
+                wave_count(cnt, kCLeaf, P.locate);
+                wave_count(cnt, kCDeep, P.locate && r.lev < ns.lds_first);
+                wave_count(cnt, kCTrunc, P.trunc);
             }
             trip_end(kPhCross);
         }
@@ -1792,54 +1865,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
             trip_begin(kPhCollide, phase == kPhCollide);
             // ---- tentative collision in the current voxel: real or null
             const bool active = phase == kPhCollide;
-            bool real = false, gathered = false, trunc = false;
-            if (active) {
-                rng.need(2, (uint32_t)pix, A.sample_base + (uint32_t)s, A.stream_base + (uint32_t)job, A.key0, A.key1);
-                const float t0 = r.t;
-                r.t = fminf(r.t + tau * __builtin_amdgcn_rcpf(r.khat), r.texit);
-                const float u = rng.take();
-                const float thr = u * r.khat;
-                const float kmin = r.kmin + path_kg();
-                // a sun ray by delta tracking is stopped below the voxel's minimum
-                // without reading k; a level-0 voxel is one cell: k is known
-                const bool below = kSun == 0 && shadow && thr < kmin;
-                float kx = r.kmin;
-                gathered = (r.lev != 0) & !below;
-                if (gathered) kx = collision_k(g, r, r.t);
-                if (kSun != 0 && shadow) {
-                    // ratio tracking (control 0) or residual ratio tracking (control
-                    // = the voxel minimum; r.khat then holds the residual majorant):
-                    // every tentative collision scales the estimate t_sun by
-                    // 1 - (k - k_ctrl) / khat, the control part by exp(-k_ctrl dt)
-                    const float kctrl = kSun == 2 ? kmin : 0.0f;
-                    t_sun *= __expf(-kctrl * (r.t - t0)) *
-                             fmaxf(0.0f, 1.0f - (kx + path_kg() - kctrl) * __builtin_amdgcn_rcpf(r.khat));
-                    if (t_sun < kSunRoulette)       // Russian roulette on small estimates
-                        t_sun = u * kSunRoulette < t_sun ? kSunRoulette : 0.0f;
-                    real = t_sun == 0.0f;
-                } else {
-                    if (!below) kc_hit = kx;
-                    real = below | (thr < kx + path_kg());
-                }
-                if (real) {
-                    res = kReal;
-                    phase = kPhEvent;
-                } else {
-                    tau = rng.take_exp1();
-                    phase = voxel_phase(r, tau);
-                    if (++segs >= A.op.max_segments) {
-                        trunc = true;
-                        phase = kPhSample;
-                    }
-                }
-            }
+            P.real = P.gathered = P.trunc = false;
+            if (active) P.collision(A, [&]() { return collision_k(g, r, r.t); });
             if (stats) {
                 wave_count(cnt, kCSegments, active);
                 wave_count(cnt, kCTentative, active);
-                wave_count(cnt, kCReals, real);
-                wave_count(cnt, kCNulls, active && !real);
-                wave_count(cnt, kCGathers, gathered);
-                wave_count(cnt, kCTrunc, trunc);
+                wave_count(cnt, kCReals, P.real);
+                wave_count(cnt, kCNulls, active && !P.real);
+                wave_count(cnt, kCGathers, P.gathered);
+                wave_count(cnt, kCTrunc, P.trunc);
             }
             trip_end(kPhCollide);
         }
@@ -1903,10 +1937,332 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
     }
 }
 
+// The last paths of a render, handed over by waves with few left once the queues
+// had drained.  The time is the serial chain of the longest path (2660
+// scatterings on the ragged field), so a path takes four lanes (QuadRay): 16 paths
+// a wave, no choice of phases and no queue; a ray that starts in the voxel of its
+// event reads nothing.  (Guided paths stay in the main kernel: here a tile held 16
+// paths at most and the network's registers left 3 waves a SIMD: 15.0 ms against
+// 14.0 at the cumulus view of 512^2 pixels, 32 samples.)
+// Measured against the main kernel running all phases in one trip below 16 paths
+// (ms): 505 k paths over a ragged field 12.2 -> 7.3, 65 k over a blob 0.99 -> 0.68,
+// 6.3 M of a batch of 48 views 35.8 -> 31, 67 M over a cumulus field 26.2 -> 23.1.
+// A lone wave issues an instruction every 7 to 8 cycles whatever its kind, so what
+// is left is the count of instructions on the way from one scattering to the next.
+template <int kMode, int kSun, bool kExt>
+__global__ __launch_bounds__(256) void render_tail_kernel(RenderArgs A)
+{
+    extern __shared__ __align__(16) float2 s_nodes[];
+    __shared__ int s_off[NC_MAX_LEVELS + 2];
+    __shared__ int4 s_rows[NC_MAX_LEVELS + 2];
+    __shared__ RareShared s_rare;
+    __shared__ __align__(16) uint32_t s_rng[4 * 16 * 16];
+    static_assert(kMode != kGuided, "guided paths end in the main kernel");
+    const unsigned int count = *A.tail_count;
+    const unsigned int waves = gridDim.x * 4u, wave = blockIdx.x * 4u + (threadIdx.x >> 6);
+    if (blockIdx.x * 4u >= count) return;   // (workgroup-uniform)
+    if (threadIdx.x == 0) stage_rare(*A.rare, s_rare);
+    stage_levels(A.g, A.lds_first, A.lds_nodes, s_nodes, s_off, s_rows);   // ends with a block barrier
+    const NodeSrc ns{A.g.nodes, s_nodes, s_off, A.lds_first, 0, A.g.n[0], A.g.n[1], s_rows};
+    const JobView *const jobs = lds_get(s_rare.jobs);
+    QuadGrid G;
+    G.init(A.g, s_rows);
+    const int ax = G.ax, quad = (int)(__lane_id() >> 2);
+    const HGc &hg = A.op.hg;
+    const int max_scatter = A.op.max_scatter;
+    constexpr int kEventDraws = 3;
+    auto on_axis = [&](const float v[3]) { return quad_pick(ax, v[0], v[1], v[2]); };
+    const float gpos = quad_pick(ax, A.gpos[0], A.gpos[1], A.gpos[2]);
+    // the wave's paths: wave, wave + waves, ... one per quad
+    for (unsigned long long first = wave; first < count; first += 16ull * waves) {
+        const unsigned long long i = first + (unsigned long long)quad * waves;
+        QuadRay r;
+        RngQuad rng;
+        rng.buf = s_rng + (threadIdx.x >> 2) * 16u;
+        int phase = kPhIdle, job = 0, pix = 0, s = 0, order = 0, segs = 0, res = 0;
+        bool shadow = false, ground_ev = false, start = false;
+        float acc = 0.0f, acc2 = 0.0f, Lp = 0.0f, tau = 0.0f, kc_hit = 0.0f, w_nee = 0.0f, p_cont = 0.0f;
+        float beta = 1.0f, kev = 0.0f, kg = A.g.k_gas, pd = 0.0f, sun = 0.0f;
+        float &t_sun = kc_hit;
+        auto path_kg = [&]() { return kExt ? kg : A.g.k_gas; };
+        auto draws = [&](int k) __attribute__((always_inline)) {
+            rng.need(k, (uint32_t)pix, A.sample_base + (uint32_t)s, A.stream_base + (uint32_t)job, A.key0, A.key1);
+        };
+        r.vc = -1;
+        r.vlev = 0;
+        r.vkmin = r.vkhat = 0.0f;
+        auto enter = [&]() __attribute__((always_inline)) {
+            r.enter(G);
+            if (kSun == 2 && shadow) r.khat = fmaxf(r.khat - (r.kmin + path_kg()), 0.0f);
+            phase = ((r.khat > 0.0f) & (tau < r.khat * (r.texit - r.t))) ? kPhCollide : kPhCross;
+        };
+        if (i < count) {
+            const uint32_t *w = A.tail + i;
+            const size_t cap = A.tail_cap;
+            auto get_i = [&](int k) { return (int)w[(size_t)k * cap]; };
+            auto get_f = [&](int k) { return __uint_as_float(w[(size_t)k * cap]); };
+            const int fl = get_i(kTwFlags);
+            phase = fl & 7;
+            shadow = (fl & 8) != 0;
+            ground_ev = (fl & 16) != 0;
+            res = (fl >> 5) & 3;
+            r.lev = (fl >> 12) & 0xff;
+            job = get_i(kTwInts);
+            pix = get_i(kTwInts + 1);
+            s = get_i(kTwInts + 2);
+            order = get_i(kTwInts + 3);
+            segs = get_i(kTwInts + 4);
+            acc = get_f(kTwFloats);
+            acc2 = get_f(kTwFloats + 1);
+            Lp = get_f(kTwFloats + 2);
+            tau = get_f(kTwFloats + 3);
+            kc_hit = get_f(kTwFloats + 4);
+            w_nee = get_f(kTwFloats + 5);
+            p_cont = get_f(kTwFloats + 6);
+            r.t = get_f(kTwFloats + 7);
+            r.tend = get_f(kTwFloats + 8);
+            r.texit = get_f(kTwFloats + 9);
+            r.khat = get_f(kTwFloats + 10);
+            r.kmin = get_f(kTwFloats + 11);
+            beta = get_f(kTwFloats + 12);   // (an irradiance sensor's paths have a weight too)
+            if (kMode == kCollect) kev = get_f(kTwFloats + 13);
+            if (kExt) kg = get_f(kTwFloats + 14);
+            r.o = get_f(kTwAxes + 5 * ax);
+            r.d = get_f(kTwAxes + 5 * ax + 1);
+            pd = get_f(kTwAxes + 5 * ax + 2);
+            sun = get_f(kTwAxes + 5 * ax + 3);
+            r.c = get_i(kTwAxes + 5 * ax + 4);
+            {
+                const float d3[3] = {r.d, r.d, r.d};
+                float inv3[3];
+                ray_inverse(d3, inv3);
+                r.inv = inv3[0];
+            }
+            rng.resume((uint32_t)get_i(kTwDraw), fl >> 20, (uint32_t)pix, A.sample_base + (uint32_t)s,
+                       A.stream_base + (uint32_t)job, A.key0, A.key1);
+            if (phase == kPhRay) {
+                r.locate(A.g, G, ns, A.op.mscale);
+                enter();
+            } else {
+                // a cell of the current voxel from the one past it
+                if ((fl >> (8 + ax)) & 1) r.c -= r.d > 0.0f ? 1 : -1;
+                r.faces(G);
+            }
+        }
+        // across the exit face into the next voxel, or the ray's end
+        auto cross = [&]() __attribute__((always_inline)) {
+            const float dt = r.texit - r.t;
+            tau -= r.khat * dt;
+            bool spent = false;
+            if (kSun == 2 && shadow) {
+                t_sun *= __expf(-(r.kmin + path_kg()) * dt);
+                if (t_sun < kSunRoulette) {     // Russian roulette on small estimates
+                    draws(1);
+                    t_sun = rng.take() * kSunRoulette < t_sun ? kSunRoulette : 0.0f;
+                }
+                spent = t_sun == 0.0f;
+            }
+            res = spent ? kReal : kExit;
+            r.t = r.texit;
+            phase = kPhEvent;
+            if (spent | !(r.t < r.tend)) return;
+            r.next_cell(G);
+            r.locate(A.g, G, ns, A.op.mscale);
+            enter();
+            if (++segs >= A.op.max_segments) phase = kPhSample;   // stop the path
+        };
+        // as PathState::collision
+        auto collide = [&]() __attribute__((always_inline)) {
+            draws(2);
+            const float t0 = r.t;
+            r.t = fminf(r.t + tau * __builtin_amdgcn_rcpf(r.khat), r.texit);
+            const float u = rng.take();
+            const float thr = u * r.khat;
+            const float kmin = r.kmin + path_kg();
+            const bool below = kSun == 0 && shadow && thr < kmin;
+            float kx = r.kmin;
+            if ((r.lev != 0) & !below) kx = r.k_at(A.g, G);
+            bool real;
+            if (kSun != 0 && shadow) {
+                const float kctrl = kSun == 2 ? kmin : 0.0f;
+                t_sun *= __expf(-kctrl * (r.t - t0)) *
+                         fmaxf(0.0f, 1.0f - (kx + path_kg() - kctrl) * __builtin_amdgcn_rcpf(r.khat));
+                if (t_sun < kSunRoulette) t_sun = u * kSunRoulette < t_sun ? kSunRoulette : 0.0f;
+                real = t_sun == 0.0f;
+            } else {
+                if (!below) kc_hit = kx;
+                real = below | (thr < kx + path_kg());
+            }
+            if (real) {
+                res = kReal;
+                phase = kPhEvent;
+            } else {
+                tau = rng.take_exp1();
+                phase = ((r.khat > 0.0f) & (tau < r.khat * (r.texit - r.t))) ? kPhCollide : kPhCross;
+                if (++segs >= A.op.max_segments) phase = kPhSample;
+            }
+        };
+        // the local estimate's direction drawn in the solar disc's cone
+        auto disc = [&]() __attribute__((always_inline)) {
+            const JobView &J = jobs[job];
+            const float s0[3] = {J.sun[0], J.sun[1], J.sun[2]};
+            const float c1 = rng.take(), c2 = rng.take();
+            float v[3];
+            cone_dir(s0, A.op.cone_cos, c1, c2, v);
+            sun = on_axis(v);
+        };
+        // as PathState::event
+        auto event = [&]() __attribute__((always_inline)) {
+            const bool cone = kExt && A.op.cone;
+            if (cone) draws(kEventDraws);
+            bool cont = false;
+            if (shadow) {
+                if (res == kExit) Lp += beta * w_nee * (kSun != 0 ? t_sun : 1.0f);
+                cont = true;
+            } else {
+                const bool volume = res == kReal;
+                const float dz = quad_axis<2>(r.d);
+                if (!volume & !(dz < 0.0f)) {
+                    if (cone && order == 0 && !ground_ev) {
+                        const JobView &J = jobs[job];
+                        const float s0[3] = {J.sun[0], J.sun[1], J.sun[2]};
+                        if (quad_sum(r.d * on_axis(s0)) >= A.op.cone_cos) Lp += beta * A.op.cone_L;
+                    }
+                    phase = kPhSample;
+                } else {
+                    pd = r.d;
+                    float gain = 1.0f;
+                    if (volume) {
+                        r.keep_voxel();   // (a path ray's majorant is the voxel's own)
+                        r.o = r.o + r.t * r.d;
+                        const float kd = kc_hit;
+                        kev = kd + path_kg();
+                        const float ssa = A.op.ssa * kd * __builtin_amdgcn_rcpf(kd + path_kg());
+                        if (cone) {
+                            disc();
+                            gain = A.op.cone_gain;
+                        }
+                        const float mu = quad_sum(pd * sun);
+                        w_nee = ssa * (kExt ? phase_eval(hg, A.op.tab, mu) : hg_phase(hg, mu)) * gain;
+                        p_cont = ssa;
+                    } else {
+                        const float tg = -quad_axis<2>(r.o) * __builtin_amdgcn_rcpf(dz);
+                        r.o = ax == 2 ? 0.0f : r.o + tg * r.d;
+                        const float rho = jobs[job].rho;
+                        if (cone) {
+                            disc();
+                            gain = A.op.cone_gain;
+                        }
+                        w_nee = rho * (1.0f / kPi) * quad_axis<2>(sun) * gain;
+                        p_cont = rho;
+                    }
+                    ground_ev = !volume;
+                    ++order;
+                    if (max_scatter >= 0 && order > max_scatter) {
+                        phase = kPhSample;
+                    } else if (w_nee > 0.0f) {
+                        shadow = true;
+                        start = true;
+                    } else {
+                        cont = true;
+                    }
+                }
+            }
+            if (!cont) {
+                if (!cone) rng.skip(kEventDraws);
+                return;
+            }
+            shadow = false;
+            draws(kEventDraws);
+            if (max_scatter >= 0 && order >= max_scatter) {
+                phase = kPhSample;
+            } else if (rng.take() >= p_cont) {
+                phase = kPhSample;
+            } else {
+                const float u1 = rng.take(), u2 = rng.take();
+                const float win = pd;
+                float v[3] = {quad_axis<0>(pd), quad_axis<1>(pd), quad_axis<2>(pd)};
+                if (ground_ev)
+                    lambert(v, u1, u2);
+                else
+                    turn(v, kExt ? phase_sample_mu(hg, A.op.tab, u1) : hg_sample_mu(hg, u1), u2);
+                pd = on_axis(v);
+                start = true;
+                if (kMode == kCollect && !ground_ev) {
+                    unsigned int k0 = 0, k1 = 0;
+                    if (G.ql == 0) {
+                        const unsigned long long k = atomicAdd(A.col.count, 1ull);
+                        k0 = (unsigned int)k;
+                        k1 = (unsigned int)(k >> 32);
+                    }
+                    const unsigned long long k = ((unsigned long long)(unsigned int)quad_axis<0>((int)k1) << 32) |
+                                                 (unsigned int)quad_axis<0>((int)k0);
+                    if (k < A.col.cap) {
+                        float *q = A.col.records + k * kGuideRecord;
+                        q[ax] = (r.o - G.lo) * gpos - 1.0f;
+                        q[3 + ax] = win;
+                        q[7 + ax] = pd;
+                        if (G.ql == 0) {
+                            q[6] = __logf(1.0f + kev);
+                            q[10] = Lp;
+                            q[11] = __uint_as_float((uint32_t)(pix * A.col_spp + s));
+                        }
+                    }
+                }
+            }
+        };
+        auto ray_start = [&]() __attribute__((always_inline)) {
+            draws(1);
+            const bool hit = r.setup(G, shadow ? sun : pd);
+            if (kSun != 0 && shadow) t_sun = 1.0f;
+            tau = rng.take_exp1();
+            if (hit) {
+                r.first_voxel(A.g, G, ns, A.op.mscale);
+                enter();
+            } else {
+                // misses the box: the next step finds the ray outside
+                r.t = r.tend = r.texit = 0.0f;
+                r.khat = 0.0f;
+                r.kmin = 0.0f;
+                r.lev = 0;
+                phase = kPhCross;
+            }
+        };
+        while (__ballot(phase < kPhSample)) {
+            // (one loop, in which every path of the wave takes its next step: with a
+            // loop over each ray's voxels inside, a path in a dense cloud would
+            // wait at every ray for the wave's longest)
+            if (phase == kPhEvent) {
+                start = false;
+                event();
+                if (start) ray_start();
+            }
+            if (phase == kPhCross) cross();
+            if (phase == kPhCollide) collide();
+        }
+        if (phase == kPhSample && G.ql == 0) {
+            // the path's end, as the renderer's sample phase adds it
+            const JobView &J = jobs[job];
+            if (kMode == kCollect) A.col.final_L[(size_t)pix * A.col_spp + s] = Lp;
+            acc += Lp;
+            acc2 += Lp * Lp;
+            const unsigned long long q = J.out_off + (unsigned long long)pix;
+            const double S = (double)J.S;
+            unsafeAtomicAdd(lds_get(s_rare.sum) + q, S * (double)acc);
+            unsafeAtomicAdd(lds_get(s_rare.sumsq) + q, S * S * (double)acc2);
+        }
+    }
+}
+
 __global__ void zero_u64_kernel(unsigned long long *p, int n)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0ull;
+}
+
+void launch_zero_u64(const nc_ctx *ctx, unsigned long long *p, int n)
+{
+    hipLaunchKernelGGL(zero_u64_kernel, dim3((n + 63) / 64), dim3(64), 0, ctx->stream, p, n);
 }
 
 __global__ void collect_finish_kernel(CollectView cv)
@@ -1927,6 +2283,20 @@ hipError_t launch_collect_finish(const nc_ctx *ctx, const CollectView &cv)
     return hipGetLastError();
 }
 
+template <int kMode, bool kExt>
+static const void *tail_variant(int est)
+{
+    return est == 0   ? (const void *)render_tail_kernel<kMode, 0, kExt>
+           : est == 1 ? (const void *)render_tail_kernel<kMode, 1, kExt>
+                      : (const void *)render_tail_kernel<kMode, 2, kExt>;
+}
+
+static const void *tail_kernel(int mode, int est, bool ext)
+{
+    if (mode == kCollect) return ext ? tail_variant<kCollect, true>(est) : tail_variant<kCollect, false>(est);
+    return ext ? tail_variant<kPlain, true>(est) : tail_variant<kPlain, false>(est);
+}
+
 hipError_t launch_render(const nc_ctx *ctx, const nc_grid *g, const float *d_kc, const OptView &op,
                          const JobView *jobs_host, int n_jobs, const nc_sampling &s, double *sum, double *sumsq,
                          nc_counters *counters, const RenderScratch &scr, const nc_guide *const *guides,
@@ -1934,6 +2304,7 @@ hipError_t launch_render(const nc_ctx *ctx, const nc_grid *g, const float *d_kc,
 {
     const int mode = guides ? kGuided : collect ? kCollect : kPlain;
     const int block0 = ctx->launch.block > 0 ? std::max(64, std::min(256, (ctx->launch.block / 64) * 64)) : 256;
+    const bool ext = op.kd_n > 0 || op.tab.n > 0 || op.cone;   // the extended medium: its own kernel variants
     const size_t guide_bytes =
         mode == kGuided ? (size_t)kGuideWeightBytes + (size_t)(block0 / 64) * kGuideScratchPerWave : 0;
     Shape sh = choose_shape(ctx, g, 256, guide_bytes, 0);
@@ -1990,6 +2361,12 @@ hipError_t launch_render(const nc_ctx *ctx, const nc_grid *g, const float *d_kc,
     A.counters = counters;
     rare.queue = scr.queue;
     A.n_sets = n_sets;
+    // (no tail kernel where statistics are kept, for guided paths, on a grid too
+    // large for its arithmetic, or without memory for it)
+    const bool tail = scr.tail && !counters && mode != kGuided && A.g.narrow;
+    A.tail = tail ? scr.tail : nullptr;
+    A.tail_count = reinterpret_cast<unsigned int *>(scr.queue + 8);   // in the first queue head's line, zeroed with it
+    A.tail_cap = kTailCap;
     for (int k = 0; k <= n_sets; ++k)
         rare.set_begin[k] = set_first_job[k] < n_jobs ? jobs[set_first_job[k]].item_begin : items;
     for (int k = 0; k < n_sets; ++k) {
@@ -2026,8 +2403,7 @@ hipError_t launch_render(const nc_ctx *ctx, const nc_grid *g, const float *d_kc,
     // kernel variant: mode, sun-ray estimator, register budget (waves per SIMD)
     const int est = s.flags & NC_SUN_ESTIMATOR_MASK;
     const void *fn = nullptr;
-    if (op.kd_n > 0 || op.tab.n > 0 || op.cone) {
-        // the extended medium (k-distribution, phase table, solar disc): its own kernel variants
+    if (ext) {
         if (mode == kGuided && n_sets > 1)
             fn = est == 0 ? (const void *)render_kernel<4, kGuided, 0, true, true>
                  : est == 1 ? (const void *)render_kernel<4, kGuided, 1, true, true>
@@ -2089,8 +2465,16 @@ hipError_t launch_render(const nc_ctx *ctx, const nc_grid *g, const float *d_kc,
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(zero_u64_kernel, dim3(2 * n_sets), dim3(64), 0, ctx->stream, scr.queue, 128 * n_sets);
     if (collect) hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, ctx->stream, collect->count, 1);
+    // (a launch of hardly more than a path per lane is all tail: earlier there)
+    A.tail_lanes = items <= 2ull * wgs * sh.block ? 2 * kTailLanes : kTailLanes;
+    const long long tail_paths = (long long)wgs * (sh.block / 64) * A.tail_lanes;   // at most
+    if (tail_paths > (long long)kTailCap) A.tail = nullptr;
     void *args[] = {&A};
-    return hipLaunchKernel(fn, dim3(wgs), dim3(sh.block), args, lds, ctx->stream);
+    e = hipLaunchKernel(fn, dim3(wgs), dim3(sh.block), args, lds, ctx->stream);
+    if (e != hipSuccess || !A.tail) return e;
+    const int tail_waves = (int)std::min<long long>(tail_paths, kTailWaves);
+    return hipLaunchKernel(tail_kernel(mode, est, ext), dim3((tail_waves + 3) / 4), dim3(256), args, node_bytes,
+                           ctx->stream);
 }
 
 // Error of an image estimate over b x b pixel blocks (b = 1: per pixel):

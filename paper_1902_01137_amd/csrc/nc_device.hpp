@@ -162,6 +162,42 @@ struct RngBuf {
     __device__ float take_exp1() { return neg_log_unit(1.0f - take()); }
 };
 
+// A path's random stream kept per lane as a ring of four Philox blocks in LDS,
+// for a kernel whose phases take several numbers at once without dropping any:
+// before a phase that takes up to k numbers (k <= 12) the caller fills the ring
+// where it holds fewer, and since a block costs a wave the same for one lane as
+// for all, every lane with a free slot then computes its next block.  The
+// numbers and their order are Rng's.  Layout [block % 4][word][lane]: a lane
+// always falls on its own bank.
+struct RngRing {
+    static constexpr uint32_t kBlocks = 4;
+    static constexpr int kWordsPerWave = kBlocks * 4 * 64;
+    uint32_t *q;      // the lane's column of the wave's ring
+    uint32_t head;    // next number of the stream (4 block + word)
+    uint32_t gen;     // blocks computed so far
+
+    __device__ void reset() { head = gen = 0; }
+    __device__ bool holds(uint32_t k) const { return head + k <= 4u * gen; }
+    __device__ bool space() const { return gen < (head >> 2) + kBlocks; }
+    __device__ void fill(uint32_t a, uint32_t b, uint32_t stream, uint32_t k0, uint32_t k1)
+    {
+        const U4 r = philox4x32_10_uk(U4{a, b, gen, stream}, k0, k1);
+        uint32_t *w = q + (gen & (kBlocks - 1u)) * 256u;
+        w[0] = r.x;
+        w[64] = r.y;
+        w[128] = r.z;
+        w[192] = r.w;
+        ++gen;
+    }
+    __device__ float take()
+    {
+        const uint32_t v = q[(head & (4u * kBlocks - 1u)) * 64u];
+        ++head;
+        return (float)(v >> 8) * 5.9604644775390625e-08f;
+    }
+    __device__ float take_exp1() { return neg_log_unit(1.0f - take()); }
+};
+
 // ---------------------------------------------------------------------------
 // Grid as seen by the kernels.
 // Nodes of levels 1..L are stored level after level, each level [z][y][x]
@@ -808,45 +844,6 @@ __device__ inline void stage_levels(const GridView &g, int lds_first, int lds_no
         for (int i = threadIdx.x; i < lds_nodes; i += blockDim.x) s_nodes[i] = g.nodes[base + i];
     }
     __syncthreads();
-}
-
-// The voxel a ray was in when it stopped at an event; a new ray leaving the
-// event point starts in the same voxel unless rounding put its origin in a
-// neighbouring cell, which the check below detects.
-struct VoxelCache {
-    int lev, i0, i1, i2;
-    float khat, kmin;
-};
-
-__device__ inline VoxelCache voxel_of(const Ray &r)
-{
-    return VoxelCache{r.lev, r.c[0] >> r.lev, r.c[1] >> r.lev, r.c[2] >> r.lev, r.khat, r.kmin};
-}
-
-__device__ inline void start_ray_cached(const GridView &g, const NodeSrc &ns, Ray &r, const float o[3],
-                                        const float d[3], const VoxelCache &vc, float mscale, Counters &cnt)
-{
-    if (ray_setup(g, r, o, d, 0.0f)) {
-        if ((r.c[0] >> vc.lev) == vc.i0 && (r.c[1] >> vc.lev) == vc.i1 && (r.c[2] >> vc.lev) == vc.i2) {
-            r.lev = vc.lev;
-            r.khat = vc.khat;
-            r.kmin = vc.kmin;
-            leaf_exit(g, r);
-        } else {
-            find_leaf(g, ns, r, mscale, cnt.node_reads);
-        }
-        ++cnt.leaf_visits;
-    } else {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            r.o[a] = o[a];
-            r.d[a] = d[a];
-        }
-        r.t = r.tend = r.texit = 0.0f;
-        r.khat = 0.0f;
-        r.kmin = 0.0f;
-        r.lev = vc.lev;
-    }
 }
 
 // ---------------------------------------------------------------------------

@@ -58,9 +58,9 @@ __device__ inline U4 philox4x32_10_uk(U4 c, uint32_t k0, uint32_t k1)
     return philox4x32_10(c, k0, k1);
 }
 
-// -ln(w) for w in (0, 1] that is a multiple of 2^-24: the steps of __logf with
-// the ones for subnormal, infinite and NaN arguments left out (the same value
-// for all 2^24 arguments, up to the sign of -ln(1) = 0).
+// -ln(w) for w in (0, 1] that is a multiple of 2^-24: the hardware's log2 times
+// ln 2 in two floats (no subnormal, infinite or NaN argument to care for; the
+// value of -__logf for all 2^24 arguments, up to the sign of -ln(1) = 0).
 __device__ inline float neg_log_unit(float w)
 {
     const float y = -__builtin_amdgcn_logf(w);   // (log2)
@@ -71,65 +71,9 @@ __device__ inline float neg_log_unit(float w)
 
 // A path's random stream: counter = (a, b, draw, stream), key = seed.  Each
 // Philox call yields four uniforms, consumed in order.
-struct Rng {
-    uint32_t a, b, stream, draw;
-    uint32_t k0, k1;
-    uint32_t q0, q1, q2, q3;
-    int left;
-
-    __device__ void init(uint32_t a_, uint32_t b_, uint32_t stream_, uint64_t seed)
-    {
-        a = a_;
-        b = b_;
-        stream = stream_;
-        draw = 0;
-        k0 = (uint32_t)seed;
-        k1 = (uint32_t)(seed >> 32);
-        left = 0;
-    }
-    // uniform in [0, 1) with 24 random bits
-    __device__ float u01()
-    {
-        if (left == 0) {
-            U4 r = philox4x32_10_uk(U4{a, b, draw, stream}, k0, k1);
-            ++draw;
-            q0 = r.x; q1 = r.y; q2 = r.z; q3 = r.w;
-            left = 4;
-        }
-        const uint32_t v = q0;
-        q0 = q1; q1 = q2; q2 = q3;
-        --left;
-        return (float)(v >> 8) * 5.9604644775390625e-08f;
-    }
-    // optical thickness ~ Exp(1)
-    __device__ float exp1() { return neg_log_unit(1.0f - u01()); }
-
-    // Batched draws: need(k) makes sure k uniforms are buffered (a fresh
-    // Philox block replaces a buffer holding fewer), take() consumes one
-    // without a check.  One refill site per caller keeps the Philox rounds
-    // out of divergent branches.
-    __device__ void need(int k)
-    {
-        if (left < k) {
-            U4 r = philox4x32_10_uk(U4{a, b, draw, stream}, k0, k1);
-            ++draw;
-            q0 = r.x; q1 = r.y; q2 = r.z; q3 = r.w;
-            left = 4;
-        }
-    }
-    __device__ float take()
-    {
-        const uint32_t v = q0;
-        q0 = q1; q1 = q2; q2 = q3;
-        --left;
-        return (float)(v >> 8) * 5.9604644775390625e-08f;
-    }
-    __device__ float take_exp1() { return neg_log_unit(1.0f - take()); }
-};
-
-// The same stream with its counter words supplied by the caller at each
-// refill (the renderer rebuilds them from its pixel, sample and job), so a
-// lane keeps only the draw index and the four buffered words.
+// The counter words a, b and stream are supplied by the caller at each refill
+// (the renderer rebuilds them from its pixel, sample and job), so a lane keeps
+// only the draw index and the four buffered words.
 struct RngBuf {
     uint32_t draw;
     uint32_t q0, q1, q2, q3;
@@ -167,7 +111,7 @@ struct RngBuf {
 // before a phase that takes up to k numbers (k <= 12) the caller fills the ring
 // where it holds fewer, and since a block costs a wave the same for one lane as
 // for all, every lane with a free slot then computes its next block.  The
-// numbers and their order are Rng's.  Layout [block % 4][word][lane]: a lane
+// numbers and their order are the stream's.  Layout [block % 4][word][lane]: a lane
 // always falls on its own bank.
 struct RngRing {
     static constexpr uint32_t kBlocks = 4;
@@ -744,67 +688,8 @@ __device__ inline void wave_count(unsigned long long *s_cnt, int k, bool pred)
     if (m && __lane_id() == 0) atomicAdd(s_cnt + k, (unsigned long long)__popcll(m));
 }
 
-// ===========================================================================
-// One step of null-collision tracking in the piecewise-constant majorant
-// (Section 2.3 and Eq. 2, with the optical thickness tau carried from voxel
-// to voxel): either a tentative collision inside the current voxel, tested
-// against the true k gathered from the field, or a move to the next voxel.
-// ===========================================================================
+// How a ray's step ended.
 enum StepResult { kContinue = 0, kReal = 1, kExit = 2 };
-
-// Step outcome flags (for wave-level event counting).
-enum StepFlags : uint32_t { kFTentative = 1, kFReal = 2, kFNull = 4, kFGather = 8, kFLeaf = 16 };
-
-// One step; `reads` counts global grid/field reads, `flags` what happened.
-__device__ inline int track_step_f(const GridView &g, const NodeSrc &ns, Ray &r, float &tau, Rng &rng, float mscale,
-                                   bool shadow, float &kc_hit, uint32_t &reads, uint32_t &flags)
-{
-    const float ktau = r.khat * (r.texit - r.t);
-    if (r.khat > 0.0f && tau < ktau) {
-        r.t = fminf(r.t + tau / r.khat, r.texit);
-        const float thr = rng.u01() * r.khat;
-        bool real;
-        flags = kFTentative;
-        if (shadow && thr < g.kscale * r.kmin + g.k_gas) {
-            real = true;                      // below the voxel's minimum: real without reading k
-        } else if (r.lev == 0) {
-            kc_hit = r.kmin;                  // a level-0 voxel is one cell: k is known
-            real = thr < g.kscale * kc_hit + g.k_gas;
-        } else {
-            kc_hit = collision_k(g, r, r.t);
-            ++reads;
-            flags |= kFGather;
-            real = thr < g.kscale * kc_hit + g.k_gas;
-        }
-        if (real) {
-            flags |= kFReal;
-            return kReal;
-        }
-        flags |= kFNull;
-        tau = rng.exp1();
-        return kContinue;
-    }
-    tau -= ktau;
-    flags = 0;
-    if (!next_leaf(g, ns, r, mscale, reads)) return kExit;
-    flags = kFLeaf;
-    return kContinue;
-}
-
-__device__ inline int track_step(const GridView &g, const NodeSrc &ns, Ray &r, float &tau, Rng &rng, float mscale,
-                                 bool shadow, float &kc_hit, Counters &cnt)
-{
-    uint32_t flags = 0, rd = 0;
-    ++cnt.segments;
-    const int res = track_step_f(g, ns, r, tau, rng, mscale, shadow, kc_hit, rd, flags);
-    cnt.node_reads += rd - ((flags & kFGather) ? 1u : 0u);
-    cnt.tentative += (flags & kFTentative) ? 1 : 0;
-    cnt.reals += (flags & kFReal) ? 1 : 0;
-    cnt.nulls += (flags & kFNull) ? 1 : 0;
-    cnt.gathers += (flags & kFGather) ? 1 : 0;
-    cnt.leaf_visits += (flags & kFLeaf) ? 1 : 0;
-    return res;
-}
 
 // Start a ray; a ray that misses the box is set up to exit on its first step.
 __device__ inline void start_ray(const GridView &g, const NodeSrc &ns, Ray &r, const float o[3], const float d[3],
@@ -1045,7 +930,7 @@ struct QuadRay {
 // A path's random numbers on a quad: its lanes compute four consecutive blocks
 // at once (a quarter of the Philox instructions per block) into the quad's 16
 // words of LDS, from where a block is read when its numbers are first needed.
-// The same stream as RngBuf and Rng.
+// The same stream as RngBuf's.
 struct RngQuad {
     uint32_t *buf;               // the quad's words
     uint32_t draw;               // next block

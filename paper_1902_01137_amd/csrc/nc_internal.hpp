@@ -171,7 +171,7 @@ hipError_t launch_philox(const nc_ctx *ctx, const uint32_t *ctr, const uint32_t 
 // and the 8 work-queue heads (128 words, 16 apart, zeroed by a kernel at each
 // launch).  Either the context's buffers or the no-allocation scratch.
 constexpr size_t kRareBytes = 1536;
-// The tail kernels (the last paths of a render
+// The tail kernels (the last paths of a render call, the last photons of a flux
 // call): a wave hands its paths over when kTailLanes or fewer are left (twice as
 // many in a launch of hardly more than one path a lane), so a launch of 8192
 // waves (32 per CU) hands over kTailCap at most, each as kTailWords words at most

@@ -473,93 +473,226 @@ struct TransArgs {
     int lds_first, lds_nodes;
 };
 
-// Ratio (kctrl = 0) or residual ratio tracking (kctrl = the voxel minimum,
-// collisions sampled with the residual majorant) of one ray to the box exit.
-// The same estimators as the renderer's sun rays, as a plain loop.
-__device__ inline float ratio_transmittance(const GridView &g, const NodeSrc &ns, Ray &r, Rng &rng, float mscale,
-                                            bool resid, Counters &cnt)
-{
-    const float sun_rr = 0.1f;
-    float T = 1.0f;
-    auto kctrl = [&]() { return resid ? g.kscale * r.kmin + g.k_gas : 0.0f; };
-    if (resid) r.khat = fmaxf(r.khat - kctrl(), 0.0f);
-    float tau = rng.exp1();
-    for (;;) {
-        ++cnt.segments;
-        const float ktau = r.khat * (r.texit - r.t);
-        if (r.khat > 0.0f && tau < ktau) {
-            const float t0 = r.t;
-            r.t = fminf(r.t + tau / r.khat, r.texit);
-            const float kc = kctrl();
-            float kx = g.kscale * r.kmin + g.k_gas;
-            if (r.lev != 0) {
-                kx = g.kscale * collision_k(g, r, r.t) + g.k_gas;
-                ++cnt.gathers;
-            }
-            ++cnt.tentative;
-            ++cnt.nulls;
-            T *= __expf(-kc * (r.t - t0)) * fmaxf(0.0f, 1.0f - (kx - kc) / r.khat);
-            if (T < sun_rr) T = rng.u01() * sun_rr < T ? sun_rr : 0.0f;
-            if (T == 0.0f) return 0.0f;
-            tau = rng.exp1();
-        } else {
-            if (resid) {
-                T *= __expf(-kctrl() * (r.texit - r.t));
-                if (T < sun_rr) T = rng.u01() * sun_rr < T ? sun_rr : 0.0f;
-                if (T == 0.0f) return 0.0f;
-            }
-            tau -= ktau;
-            uint32_t rd = 0;
-            if (!next_leaf(g, ns, r, mscale, rd)) return T;
-            cnt.node_reads += rd;
-            ++cnt.leaf_visits;
-            if (resid) r.khat = fmaxf(r.khat - kctrl(), 0.0f);
-        }
-    }
-}
+// Lanes of a wave still walking at which the others are given new rays: 16 to 54
+// differ by up to 10 %, 32 is the best of them on 67 M samples.
+constexpr int kRayRefill = 32;
 
+// A lane takes one ray and up to S of its samples, and walks the ray's voxels
+// once for all of them: a sample is its optical thickness, its estimate and the
+// count of its random numbers, in registers.  Voxel after voxel every sample is
+// carried across (a few instructions); those that meet something inside (a
+// tentative collision, Russian roulette) are then taken one by one, lowest first.
+// Bound by vector instruction issue at the lanes in use: rays cross 4 voxels on
+// average and 30 or more in a cloud, so lanes whose ray has ended take the next.
+// 4.2 M rays of 16 samples over 512 x 512 x 160 cells (ms): 10.2 with a ray per lane
+// and its samples one after the other, 4.5 with 4 samples together, 2.1 with 8
+// together and the lanes refilled; 300 rays of 64 samples 1.4 and 0.07.
+template <int kEst, int S>
 __global__ __launch_bounds__(256) void transmittance_kernel(TransArgs A)
 {
     extern __shared__ __align__(16) float2 s_nodes[];
     __shared__ int s_off[NC_MAX_LEVELS + 2];
-    stage_levels(A.g, A.lds_first, A.lds_nodes, s_nodes, s_off);
-    const NodeSrc ns{A.g.nodes, s_nodes, s_off, A.lds_first, s_off[A.lds_first <= A.g.L ? A.lds_first : 0],
-                     A.g.n[0], A.g.n[1]};
+    __shared__ int4 s_rows[NC_MAX_LEVELS + 2];
+    stage_levels(A.g, A.lds_first, A.lds_nodes, s_nodes, s_off, s_rows);
+    const GridView &g = A.g;
+    const NodeSrc ns{g.nodes, s_nodes, s_off, A.lds_first, s_off[A.lds_first <= g.L ? A.lds_first : 0],
+                     g.n[0], g.n[1], s_rows};
+    constexpr float sun_rr = 0.1f;   // roulette below this estimate (survivors carry it)
+    const bool stats = A.counters != nullptr;
+    const uint32_t key0 = (uint32_t)A.seed, key1 = (uint32_t)(A.seed >> 32);
     Counters cnt = {};
-    for (long long w = blockIdx.x * (long long)blockDim.x + threadIdx.x; w < A.items;
-         w += (long long)gridDim.x * blockDim.x) {
-        const int i = (int)(w % A.n);
-        const int blk = (int)(w / A.n);
-        const int s0 = blk * A.spi, s1 = min(s0 + A.spi, A.spp);
-        const float o[3] = {A.rays[6 * i], A.rays[6 * i + 1], A.rays[6 * i + 2]};
-        const float d[3] = {A.rays[6 * i + 3], A.rays[6 * i + 4], A.rays[6 * i + 5]};
-        double acc = 0.0, acc2 = 0.0;
-        for (int s = s0; s < s1; ++s) {
-            Rng rng;
-            rng.init((uint32_t)i, (uint32_t)(A.sample_offset + s), 1u, A.seed);
-            Ray r;
-            start_ray(A.g, ns, r, o, d, A.mscale, cnt);
-            float T;
-            if (A.est == 0) {
-                float tau = rng.exp1();
-                float kc_hit = 0.0f;
-                int res;
-                do {
-                    res = track_step(A.g, ns, r, tau, rng, A.mscale, true, kc_hit, cnt);
-                } while (res == kContinue);
-                T = res == kExit ? 1.0f : 0.0f;
-            } else {
-                T = ratio_transmittance(A.g, ns, r, rng, A.mscale, A.est == 2, cnt);
+    // the wave's items, a chunk of one per lane at a time: chunks wave, wave + waves, ...
+    const int block = (int)blockDim.x >> 6;
+    const long long waves = (long long)gridDim.x * block, wave = (long long)blockIdx.x * block + (threadIdx.x >> 6);
+    long long chunk = wave;          // wave-uniform
+    int chunk_left = 64;
+    bool have = false, walking = false;
+    int i = 0, n_live = 0;
+    uint32_t sample = 0, live = 0;
+    float tau[S], T[S];
+    uint32_t drawn[S];
+    Ray r;
+    for (;;) {
+        const int n_walking = lane_count(walking);
+        if (n_walking == 0 || (n_walking <= kRayRefill && chunk * 64 < A.items)) {
+            // ---- finished rays to the outputs, then the next ones
+            if (have && !walking) {
+                double acc = 0.0, acc2 = 0.0;
+#pragma unroll
+                for (int s = 0; s < S; ++s) {
+                    const float v = (live >> s) & 1u ? T[s] : 0.0f;
+                    acc += v;
+                    acc2 += (double)v * v;
+                }
+                unsafeAtomicAdd(A.sum + i, acc);
+                unsafeAtomicAdd(A.sumsq + i, acc2);
+                have = false;
             }
-            acc += T;
-            acc2 += (double)T * T;
-            ++cnt.paths;
-            ++cnt.nee_rays;
+            const unsigned long long free = __ballot(!walking);
+            const int n_free = __popcll(free);
+            const int rank = (int)lanes_below(free);
+            const long long w = rank < chunk_left ? chunk * 64 + (64 - chunk_left) + rank
+                                                  : (chunk + waves) * 64 + (rank - chunk_left);
+            if (!walking && w < A.items) {
+                have = walking = true;
+                const int blk = A.items <= 0xffffffffll ? (int)((uint32_t)w / (uint32_t)A.n) : (int)(w / A.n);
+                i = (int)(w - (long long)blk * A.n);
+                const int s0 = blk * A.spi;
+                n_live = min(A.spi, A.spp - s0);
+                sample = (uint32_t)(A.sample_offset + s0);
+                const float o[3] = {A.rays[6 * (size_t)i], A.rays[6 * (size_t)i + 1], A.rays[6 * (size_t)i + 2]};
+                const float d[3] = {A.rays[6 * (size_t)i + 3], A.rays[6 * (size_t)i + 4], A.rays[6 * (size_t)i + 5]};
+                // samples that have ended (or are none) meet nothing: infinite thickness and estimate
+                live = (uint32_t)((1ull << n_live) - 1ull);
+#pragma unroll
+                for (int s = 0; s < S; ++s) {
+                    const U4 q = philox4x32_10_uk(U4{(uint32_t)i, sample + (uint32_t)s, 0u, 1u}, key0, key1);
+                    tau[s] = s < n_live ? neg_log_unit(1.0f - (float)(q.x >> 8) * 5.9604644775390625e-08f) : INFINITY;
+                    T[s] = s < n_live ? 1.0f : INFINITY;
+                    drawn[s] = 1u;
+                }
+                Counters c1 = {};
+                start_ray(g, ns, r, o, d, A.mscale, c1);
+                if (stats) {
+                    cnt.paths += (uint32_t)n_live;
+                    cnt.nee_rays += (uint32_t)n_live;
+                    cnt.node_reads += c1.node_reads * (uint32_t)n_live;
+                    cnt.leaf_visits += c1.leaf_visits * (uint32_t)n_live;
+                }
+            }
+            if (n_free > chunk_left) {
+                chunk += waves;
+                chunk_left = 64 - (n_free - chunk_left);
+            } else {
+                chunk_left -= n_free;
+            }
+            if (!__ballot(walking)) break;
         }
-        unsafeAtomicAdd(A.sum + i, acc);
-        unsafeAtomicAdd(A.sumsq + i, acc2);
+        const uint32_t id = (uint32_t)i;
+        if (walking) {
+            const float kmin = g.kscale * r.kmin + g.k_gas;
+            const float kctrl = kEst == 2 ? kmin : 0.0f;
+            const float khat = kEst == 2 ? fmaxf(r.khat - kctrl, 0.0f) : r.khat;
+            float ktau = khat * (r.texit - r.t);
+            asm("" : "+v"(ktau));   // (a rounded product in the comparison and the difference alike)
+            const float e = kEst == 2 ? __expf(-kctrl * (r.texit - r.t)) : 1.0f;
+            if (stats) cnt.segments += (uint32_t)__popc(live);
+            uint32_t meet = 0;
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                const float tx = T[s] * e;
+                bool m = (khat > 0.0f) & (tau[s] < ktau);
+                if (kEst == 2) m |= tx < sun_rr;
+                meet |= m ? 1u << s : 0u;
+                if (kEst == 2) T[s] = m ? T[s] : tx;
+                tau[s] = m ? tau[s] : tau[s] - ktau;
+            }
+            meet &= live;
+            while (meet) {
+                const int s = __ffs((int)meet) - 1;
+                meet &= meet - 1u;
+                float ta = tau[0], Ts = T[0];
+                uint32_t n = drawn[0];
+#pragma unroll
+                for (int k = 1; k < S; ++k) {
+                    ta = k == s ? tau[k] : ta;
+                    Ts = k == s ? T[k] : Ts;
+                    n = k == s ? drawn[k] : n;
+                }
+                U4 q{};
+                bool have = false;
+                auto u01 = [&]() __attribute__((always_inline)) {
+                    if (!have | ((n & 3u) == 0u)) {
+                        q = philox4x32_10_uk(U4{id, sample + (uint32_t)s, n >> 2, 1u}, key0, key1);
+                        have = true;
+                    }
+                    const uint32_t v = (n & 2u) ? ((n & 1u) ? q.w : q.z) : ((n & 1u) ? q.y : q.x);
+                    ++n;
+                    return (float)(v >> 8) * 5.9604644775390625e-08f;
+                };
+                float t = r.t;
+                bool ended = false;
+                for (;;) {
+                    float kt = khat * (r.texit - t);
+                    asm("" : "+v"(kt));
+                    if ((khat > 0.0f) & (ta < kt)) {
+                        // a tentative collision
+                        const float t0 = t;
+                        t = fminf(t + ta / khat, r.texit);
+                        if (kEst == 0) {
+                            const float thr = u01() * khat;
+                            float k = kmin;
+                            bool real = thr < kmin;   // below the voxel's minimum: real without reading k
+                            if (!real && r.lev != 0) {
+                                k = g.kscale * collision_k(g, r, t) + g.k_gas;
+                                if (stats) ++cnt.gathers;
+                                real = thr < k;
+                            }
+                            if (stats) {
+                                ++cnt.tentative;
+                                cnt.reals += real ? 1u : 0u;
+                                cnt.nulls += real ? 0u : 1u;
+                            }
+                            ended = real;
+                        } else {
+                            float k = kmin;
+                            if (r.lev != 0) {
+                                k = g.kscale * collision_k(g, r, t) + g.k_gas;
+                                if (stats) ++cnt.gathers;
+                            }
+                            if (stats) {
+                                ++cnt.tentative;
+                                ++cnt.nulls;
+                            }
+                            Ts *= __expf(-kctrl * (t - t0)) * fmaxf(0.0f, 1.0f - (k - kctrl) / khat);
+                            if (Ts < sun_rr) Ts = u01() * sun_rr < Ts ? sun_rr : 0.0f;
+                            ended = Ts == 0.0f;
+                        }
+                        if (ended) break;
+                        ta = neg_log_unit(1.0f - u01());
+                        if (stats) ++cnt.segments;
+                    } else {
+                        // across the exit face
+                        if (kEst == 2) {
+                            Ts *= __expf(-kctrl * (r.texit - t));
+                            if (Ts < sun_rr) Ts = u01() * sun_rr < Ts ? sun_rr : 0.0f;
+                            ended = Ts == 0.0f;
+                        }
+                        ta -= kt;
+                        break;
+                    }
+                }
+                if (ended) {
+                    live &= ~(1u << s);
+                    ta = Ts = INFINITY;
+                }
+#pragma unroll
+                for (int k = 0; k < S; ++k) {
+                    tau[k] = k == s ? ta : tau[k];
+                    T[k] = k == s ? Ts : T[k];
+                    drawn[k] = k == s ? n : drawn[k];
+                }
+            }
+            walking = live != 0u && step_cell(g, r);
+            if (walking) {
+                uint32_t reads = 0;
+                find_leaf(g, ns, r, A.mscale, reads);
+                if (stats) {
+                    cnt.node_reads += reads * (uint32_t)__popc(live);
+                    cnt.leaf_visits += (uint32_t)__popc(live);
+                }
+            }
+        }
     }
     flush_counters(cnt, A.counters);
+}
+
+template <int S>
+static const void *transmittance_variant(int est)
+{
+    return est == 0   ? (const void *)transmittance_kernel<0, S>
+           : est == 1 ? (const void *)transmittance_kernel<1, S>
+                      : (const void *)transmittance_kernel<2, S>;
 }
 
 hipError_t launch_transmittance(const nc_ctx *ctx, const nc_grid *g, const float *d_kc, const OptView &op,
@@ -572,7 +705,16 @@ hipError_t launch_transmittance(const nc_ctx *ctx, const nc_grid *g, const float
     A.rays = rays;
     A.n = n;
     A.spp = s.spp;
-    A.spi = std::max(1, std::min(s.spp, 64));
+    // Samples walked together: 8 where that leaves 4 items a resident lane, 4 where
+    // it leaves 2, 2 where it leaves one.  8 against 4 together (ms): 67 M samples
+    // 2.14 and 2.33, 8.4 M 0.42 and 0.38, 4 M 0.33 and 0.26; 4 against 2: 4 M 0.26 and
+    // 0.30, 2 M 0.20 and 0.20, 1 M 0.16 and 0.13; 2 against 1: 1 M 0.13 and 0.18,
+    // 160 k 0.09 and 0.08.  (16 spill the scalar registers and leave 3 waves: 2.6 at 67 M.)
+    const long long resident = (long long)ctx->num_cus * 16 * 64;
+    int per = 8;
+    while (per > 1 && (long long)n * ((s.spp + per - 1) / per) < resident * per / 2) per /= 2;
+    const int blocks = std::max(1, (s.spp + per - 1) / per);
+    A.spi = std::max(1, (s.spp + blocks - 1) / blocks);
     A.items = (long long)n * ((s.spp + A.spi - 1) / A.spi);
     A.seed = s.seed;
     A.sample_offset = s.sample_offset;
@@ -584,9 +726,12 @@ hipError_t launch_transmittance(const nc_ctx *ctx, const nc_grid *g, const float
     A.lds_first = sh.lds_first;
     A.lds_nodes = sh.lds_nodes;
     const int wgs = (int)std::max<long long>(1, std::min<long long>((A.items + 255) / 256, (long long)sh.wgs));
-    hipLaunchKernelGGL(transmittance_kernel, dim3(wgs), dim3(256), (size_t)sh.lds_nodes * sizeof(float2), ctx->stream,
-                       A);
-    return hipGetLastError();
+    const void *fn = A.spi <= 1   ? transmittance_variant<1>(A.est)
+                     : A.spi <= 2 ? transmittance_variant<2>(A.est)
+                     : A.spi <= 4 ? transmittance_variant<4>(A.est)
+                                  : transmittance_variant<8>(A.est);
+    void *args[] = {&A};
+    return hipLaunchKernel(fn, dim3(wgs), dim3(256), args, (size_t)sh.lds_nodes * sizeof(float2), ctx->stream);
 }
 
 // ===========================================================================

@@ -558,3 +558,27 @@ def test_kdistribution_argument_checks():
     with pytest.raises(_lib.NcError) as e:
         api.flux(c, g, kd_, op, (4, 4), 1000, Sampling(seed=1, spp=1))
     assert e.value.status == _lib.NC_ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("est", [0, 1, 2])
+@pytest.mark.parametrize("n,spp", [(7, 5), (40_001, 17), (140_000, 16), (1_050_000, 11)])
+def test_samples_walked_together_are_the_single_ones(n, spp, est):
+    """1, 2, 4 and 8 samples of a ray to a lane (by the size of the call), with
+    remainders: sample by sample the calls that take one each.  Sums of at most 17
+    float64 terms in [0, 1]."""
+    desc, k = inputs.lognormal_blob()
+    c = ctx()
+    kd = device_field(k)
+    g = api.build_grid(c, kd, desc, GridParams(1.0, 0.03, 0))
+    base = inputs.random_rays(desc, 1 << 12, seed=43, inside_frac=0.6, axis_frac=0.1)
+    rays = torch.from_numpy(base).cuda().repeat((n >> 12) + 1, 1)[:n].contiguous()
+    op = Optics(majorant_scale=1.5)
+    s, s2 = api.transmittance(c, g, kd, op, rays, Sampling(seed=9, spp=spp, flags=est, sample_offset=2))
+    r, r2 = torch.zeros_like(s), torch.zeros_like(s2)
+    for m in range(spp):
+        a, b = api.transmittance(c, g, kd, op, rays, Sampling(seed=9, spp=1, flags=est, sample_offset=2 + m))
+        r += a
+        r2 += b
+    torch.testing.assert_close(s, r, rtol=1e-14, atol=1e-14)
+    torch.testing.assert_close(s2, r2, rtol=1e-14, atol=1e-14)
+    assert n < 100 or 0.0 < float(s.mean()) < spp

@@ -1144,7 +1144,7 @@ nc_status nc_guide_forward(nc_ctx *ctx, const nc_guide *gd, const float *d_in, i
     if (n == 0) return NC_OK;
     if (!d_in || !d_out) return fail(ctx, NC_ERR_INVALID_ARG, "NULL buffer");
     DeviceGuard guard(ctx->device);
-    hipError_t e = nc::guide_forward(ctx, gd, d_in, n, stride, d_out, nullptr, nullptr, nullptr);
+    hipError_t e = nc::guide_forward(ctx, gd, d_in, n, stride, d_out);
     return e == hipSuccess ? NC_OK : hip_fail(ctx, e, "guide forward");
 }
 

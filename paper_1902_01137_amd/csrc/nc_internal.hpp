@@ -71,8 +71,7 @@ struct nc_guide {
     short *d_w[4] = {};                        // bf16 padded weights [out_pad][in_pad]
     short *d_wt[4] = {};                       // and transposed
     float *d_bias[4] = {};                     // fp32 padded biases
-    float *d_scratch = nullptr;                // training activations
-    int scratch_cap = 0;
+    float *d_scratch = nullptr;                // training: partial gradients
     long long step = 0;
 };
 
@@ -160,8 +159,7 @@ hipError_t launch_flux(const nc_ctx *ctx, const nc_grid *g, const float *d_kc, c
                        int px_nx, int px_ny, unsigned long long n_photons, const nc_sampling &s, double *tally,
                        double *glob, const double *grad, double *out, nc_counters *counters);
 hipError_t guide_pack(const nc_ctx *ctx, nc_guide *gd);
-hipError_t guide_forward(const nc_ctx *ctx, const nc_guide *gd, const float *X, int n, int rec_stride, float *Z,
-                         float *H0, float *H1, float *H2);
+hipError_t guide_forward(const nc_ctx *ctx, const nc_guide *gd, const float *X, int n, int rec_stride, float *Z);
 hipError_t guide_train_step(const nc_ctx *ctx, nc_guide *gd, const float *rec, int n, int rec_stride, float lr,
                             double *d_loss, bool apply);
 void launch_zero_u64(const nc_ctx *ctx, unsigned long long *p, int n);

@@ -209,3 +209,33 @@ def test_guided_sampling_step_is_unbiased(gf):
         exp = g * rec[v, 3:6].astype(np.float64)
         se = wd.std(axis=0) / math.sqrt(m)
         assert np.all(np.abs(wd.mean(axis=0) - exp) < 5 * se + 1e-6), (v, wd.mean(axis=0), exp, se)
+
+
+@pytest.mark.parametrize("n", [1, 15, 17, 63, 65, 4099, 150_001])
+def test_forward_of_any_tile_position(n):
+    """The last tile in part, fewer records than one workgroup takes and more
+    than all resident ones take at once: a record's outputs depend on no other record."""
+    gd = api.Guide(ctx(), seed=3)
+    gd.set_params(torch.from_numpy(G.init_params(11)))
+    base = _records(61, 5)          # (prime: every record meets every place in a tile)
+    one = gd.forward(torch.from_numpy(base).cuda())
+    out = gd.forward(torch.from_numpy(np.resize(base, (n, 12))).cuda())
+    assert torch.equal(out, one.repeat(n // 61 + 1, 1)[:n])
+
+
+@pytest.mark.parametrize("n", [15, 63, 64, 65, 129, 2049])
+def test_gradient_at_the_edges_of_a_chunk(n):
+    """Parts of the 64 records a workgroup takes at a time and of its chunk (bounds as for the whole gradient above)."""
+    gd = api.Guide(ctx(), seed=4)
+    p = G.init_params(12) * 0.5
+    gd.set_params(torch.from_numpy(p))
+    rec = _records(n, 6)
+    g, loss = gd.gradient(torch.from_numpy(rec).cuda())
+    g = g.cpu().numpy().astype(np.float64)
+    w = rec[:, 10].astype(np.float64)
+    L_ref, g_ref = G.loss_grad(p, rec[:, :7].astype(np.float64), rec[:, 7:10].astype(np.float64), w)
+    lv = loss.cpu().numpy()
+    assert lv[1] == pytest.approx(w.sum(), rel=1e-6)
+    assert lv[0] / lv[1] == pytest.approx(L_ref, rel=2e-3)
+    cos = g @ g_ref / (np.linalg.norm(g) * np.linalg.norm(g_ref))
+    assert cos > 0.999 and np.linalg.norm(g - g_ref) < 1e-2 * np.linalg.norm(g_ref), cos

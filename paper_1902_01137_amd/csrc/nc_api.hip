@@ -308,10 +308,17 @@ nc_status nc_ctx_create(int32_t device, void *hip_stream, nc_ctx **out)
         delete ctx;
         return hip_fail(nullptr, e, "hipMalloc(scratch)");
     }
+    e = hipHostMalloc(reinterpret_cast<void **>(&ctx->h_flag), sizeof(unsigned int), hipHostMallocDefault);
+    if (e != hipSuccess) {
+        (void)hipFree(ctx->d_scratch);
+        delete ctx;
+        return hip_fail(nullptr, e, "hipHostMalloc(flag)");
+    }
     // the no-allocation entry point's scratch: its address on this device, once
     e = nc::noalloc_init_device(device);
     if (e != hipSuccess) {
         (void)hipFree(ctx->d_scratch);
+        (void)hipHostFree(ctx->h_flag);
         delete ctx;
         return hip_fail(nullptr, e, "no-allocation scratch address");
     }
@@ -331,6 +338,7 @@ void nc_ctx_destroy(nc_ctx *ctx)
     if (!ctx) return;
     DeviceGuard guard(ctx->device);
     if (ctx->d_scratch) (void)hipFree(ctx->d_scratch);
+    if (ctx->h_flag) (void)hipHostFree(ctx->h_flag);
     if (ctx->d_jobs) (void)hipFree(ctx->d_jobs);
     delete ctx;
 }
@@ -359,11 +367,8 @@ nc_status nc_set_launch(nc_ctx *ctx, const nc_launch *launch)
 // synchronises (reads the check's flag back).
 static nc_status grid_fill(nc_ctx *ctx, nc_grid *g, const float *d_kc)
 {
-    unsigned int *d_bad = reinterpret_cast<unsigned int *>(ctx->d_scratch + 1);
     unsigned int h_bad = 0;
-    hipError_t e = hipMemcpyAsync(d_bad, &h_bad, sizeof(unsigned int), hipMemcpyHostToDevice, ctx->stream);
-    int *d_zc = reinterpret_cast<int *>(ctx->d_scratch + 2);
-    if (e == hipSuccess) e = nc::launch_build(ctx, g, d_kc, d_bad, d_zc);
+    hipError_t e = nc::launch_build(ctx, g, d_kc, ctx->d_scratch + 1, ctx->h_flag);
     if (e == hipSuccess && g->L == 0) {
         // a single cell: validate it on the host
         float v = 0.0f;
@@ -371,9 +376,8 @@ static nc_status grid_fill(nc_ctx *ctx, nc_grid *g, const float *d_kc)
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
         if (e == hipSuccess && (!(v >= 0.0f) || std::isinf(v))) h_bad = 1;
     }
-    if (e == hipSuccess && g->L > 0)
-        e = hipMemcpyAsync(&h_bad, d_bad, sizeof(unsigned int), hipMemcpyDeviceToHost, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+    if (e == hipSuccess && g->L > 0) h_bad = *(volatile unsigned int *)ctx->h_flag;
     if (e != hipSuccess) return hip_fail(ctx, e, "grid build");
     if (h_bad) return fail(ctx, NC_ERR_RANGE, "field holds NaN, Inf or negative extinction");
     return NC_OK;

@@ -16,6 +16,7 @@ struct nc_ctx {
     nc_launch launch{};
     void *d_jobs = nullptr;        // device job table of batched renders
     size_t jobs_cap = 0;
+    unsigned int *h_flag = nullptr;            // pinned: a word that kernels write for the host
     int num_cus = 256;
     size_t lds_per_cu = 160 * 1024;
 };
@@ -146,7 +147,9 @@ struct Shape {
 GridView grid_view(const nc_grid *g, const float *d_kc);
 Shape choose_shape(const nc_ctx *ctx, const nc_grid *g, int block_default, size_t reserve = 0, int waves_default = 0);
 
-hipError_t launch_build(const nc_ctx *ctx, nc_grid *g, const float *d_kc, unsigned int *d_bad, int *d_zc);
+// flags: two device words (zeroed by the launch); bad_out: a host word the device can write, nonzero afterwards if the
+// field holds NaN, Inf or negative values
+hipError_t launch_build(const nc_ctx *ctx, nc_grid *g, const float *d_kc, unsigned long long *flags, unsigned int *bad_out);
 hipError_t launch_phase_sample(const nc_ctx *ctx, const PhaseView &t, const float *u, int n, float *out);
 hipError_t launch_export(const nc_ctx *ctx, const nc_grid *g, int level, float *kmin, float *kmax, uint8_t *mg);
 hipError_t launch_leaf_levels(const nc_ctx *ctx, const nc_grid *g, uint8_t *out);

@@ -68,52 +68,20 @@ __device__ inline float2 encode_node(float kmin, float kmax, bool merged)
     return make_float2(__uint_as_float(b), kmax);
 }
 
-// Level l >= 2 from level l-1: min and max of the (up to) 8 children.
-__global__ void build_level_kernel(const float2 *__restrict__ child, int c0, int c1, int c2, float2 *__restrict__ out,
-                                   int d0, int d1, int d2, double k_gas, double dz_node, double tau, int crit,
-                                   LayerRule lr, int level, int nz)
-{
-    const long long total = (long long)d0 * d1 * d2;
-    for (long long id = blockIdx.x * (long long)blockDim.x + threadIdx.x; id < total;
-         id += (long long)gridDim.x * blockDim.x) {
-        const int i = (int)(id % d0);
-        const int j = (int)((id / d0) % d1);
-        const int m = (int)(id / ((long long)d0 * d1));
-        float lo = INFINITY, hi = -INFINITY;
-        for (int dm = 0; dm < 2; ++dm) {
-            const int z = 2 * m + dm;
-            if (z >= c2) break;
-            for (int dj = 0; dj < 2; ++dj) {
-                const int y = 2 * j + dj;
-                if (y >= c1) break;
-                for (int di = 0; di < 2; ++di) {
-                    const int x = 2 * i + di;
-                    if (x >= c0) break;
-                    const float2 v = child[((size_t)z * c1 + y) * c0 + x];
-                    lo = fminf(lo, node_kmin(v));
-                    hi = fmaxf(hi, v.y);
-                }
-            }
-        }
-        out[id] = encode_node(lo, hi, node_merged_rule(lo, hi, k_gas, dz_node, tau, crit, lr, level, m << level,
-                                                       min((m + 1) << level, nz) - 1));
-    }
-}
-
 // Waves (level-4 nodes along x) per workgroup of the fused pass.
 constexpr int kBuildWaves = 16;
 
-// Merge settings of the levels the fused pass builds (index 1..4).
+// Merge settings of each level (index 1..L).
 struct LevelRules {
-    double dz_node[5];
-    double tau[5];
-    int crit[5];
+    double dz_node[NC_MAX_LEVELS + 1];
+    double tau[NC_MAX_LEVELS + 1];
+    int crit;
 };
 
 __device__ inline float2 level_node(float lo, float hi, double k_gas, const LevelRules &R, const LayerRule &lr, int l,
                                     int m, int nz, bool &merged)
 {
-    merged = node_merged_rule(lo, hi, k_gas, R.dz_node[l], R.tau[l], R.crit[l], lr, l, m << l,
+    merged = node_merged_rule(lo, hi, k_gas, R.dz_node[l], R.tau[l], R.crit, lr, l, m << l,
                               min((m + 1) << l, nz) - 1);
     return encode_node(lo, hi, merged);
 }
@@ -251,50 +219,135 @@ __global__ __launch_bounds__(64 * kBuildWaves) void build_fused_kernel(const flo
         nodes[off4 + ((size_t)blockIdx.z * level_dim(ny, 4) + blockIdx.y) * level_dim(nx, 4) + X4] = n4;
 }
 
-// Mask bits of levels first..L (the levels above the fused pass), OR-ed into
-// every level-1 node's mask.  One thread per run of 8 level-1 nodes along x
-// in 4 consecutive rows (y = 4q .. 4q+3): the runs lie inside one level-4
-// node, so their ancestors from level 4 up are shared, and the 4 rows' loads
-// are in flight together.
+// Levels 5..L from the fused pass's level 4.  A workgroup builds the levels 5..8
+// below one level-8 node (8^3, 4^3, 2^3 and 1 nodes, the lower ones handed up through
+// LDS); of grids with more levels the workgroup that finishes last adds the
+// few nodes above.  Then the fused pass's verdict on the field goes to the host's
+// word.  One launch where every level had its own: those took 3 to 6 us each, of which
+// the work was a fraction (1024 x 1024 x 320 cells, 6 levels: 30 us in all, now 10).
+__global__ __launch_bounds__(256) void build_upper_kernel(float2 *__restrict__ nodes, const int *__restrict__ off, int n0,
+                                                          int n1, int n2, int L, double k_gas, LevelRules R, LayerRule lr,
+                                                          const unsigned int *bad, unsigned int *bad_out,
+                                                          unsigned int *done)
+{
+    __shared__ float2 s_node[2][512];
+    __shared__ bool s_last;
+    const int tid = (int)threadIdx.x, bx = (int)blockIdx.x, by = (int)blockIdx.y, bz = (int)blockIdx.z;
+    if (bad_out && tid == 0 && bx == 0 && by == 0 && bz == 0) *bad_out = *bad;
+    // children of node (x, y, z): the up to 8 that exist
+    auto merge = [&](const float2 v, float &lo, float &hi) __attribute__((always_inline)) {
+        lo = fminf(lo, node_kmin(v));
+        hi = fmaxf(hi, v.y);
+    };
+    auto from_level = [&](int l, int x, int y, int z) __attribute__((always_inline)) {
+        const int c0 = level_dim(n0, l - 1), c1 = level_dim(n1, l - 1), c2 = level_dim(n2, l - 1);
+        const float2 *child = nodes + off[l - 1];
+        float lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            // (a child that is not there stands for its neighbour that is)
+            const int cx = min(2 * x + (k & 1), c0 - 1), cy = min(2 * y + ((k >> 1) & 1), c1 - 1),
+                      cz = min(2 * z + (k >> 2), c2 - 1);
+            merge(child[((size_t)cz * c1 + cy) * c0 + cx], lo, hi);
+        }
+        bool mg;
+        const float2 v = level_node(lo, hi, k_gas, R, lr, l, z, n2, mg);
+        nodes[off[l] + ((size_t)z * level_dim(n1, l) + y) * level_dim(n0, l) + x] = v;
+        return v;
+    };
+    for (int l = 5; l <= min(L, 8); ++l) {
+        const int w = 8 - l, side = 1 << w;       // the workgroup's nodes of level l per axis
+        const int d0 = level_dim(n0, l), d1 = level_dim(n1, l), d2 = level_dim(n2, l);
+        const float2 *below = s_node[(l & 1) ^ 1];
+        for (int e = tid; e < 1 << (3 * w); e += 256) {
+            const int ex = e & (side - 1), ey = (e >> w) & (side - 1), ez = e >> (2 * w);
+            const int x = (bx << w) + ex, y = (by << w) + ey, z = (bz << w) + ez;
+            float2 v = make_float2(INFINITY, -INFINITY);   // (none: changes no minimum and no maximum)
+            if (x < d0 && y < d1 && z < d2) {
+                if (l == 5) {
+                    v = from_level(l, x, y, z);
+                } else {
+                    float lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+                    for (int k = 0; k < 8; ++k)
+                        merge(below[((((2 * ez + (k >> 2)) << (w + 1)) + 2 * ey + ((k >> 1) & 1)) << (w + 1)) + 2 * ex + (k & 1)],
+                              lo, hi);
+                    bool mg;
+                    v = level_node(lo, hi, k_gas, R, lr, l, z, n2, mg);
+                    nodes[off[l] + ((size_t)z * d1 + y) * d0 + x] = v;
+                }
+            }
+            s_node[l & 1][e] = v;
+        }
+        __syncthreads();
+    }
+    if (L <= 8) return;
+    // (release the workgroup's nodes, acquire everyone's)
+    if (tid == 0)
+        s_last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) ==
+                 gridDim.x * gridDim.y * gridDim.z - 1u;
+    __syncthreads();
+    if (!s_last) return;
+    for (int l = 9; l <= L; ++l) {
+        const int d0 = level_dim(n0, l), d1 = level_dim(n1, l), d2 = level_dim(n2, l);
+        for (long long e = tid; e < (long long)d0 * d1 * d2; e += 256)
+            from_level(l, (int)(e % d0), (int)(e / d0 % d1), (int)(e / ((long long)d0 * d1)));
+        __threadfence();
+        __syncthreads();
+    }
+}
+
+// Mask bits of levels 5..L (the levels above the fused pass) into every level-1
+// node's mask.  One thread per run of 8 level-1 nodes along x in 16 consecutive
+// rows: they lie inside one level-5 node, so their ancestors from there up are
+// shared.  kNested: a merged node's children are merged too (true of every
+// criterion but the layered grid's), so the mask follows from the highest merged
+// level and is written without being read (1024 x 1024 x 320 cells: 32 us, now 15).
+template <bool kNested>
 __global__ void mask_upper_kernel(const float2 *__restrict__ nodes, const int *__restrict__ off, int n0, int n1,
-                                  int n2, int L, int first, uint16_t *__restrict__ mask)
+                                  int n2, int L, uint16_t *__restrict__ mask)
 {
     const int d0 = level_dim(n0, 1), d1 = level_dim(n1, 1), d2 = level_dim(n2, 1);
-    const int runs = (d0 + 7) >> 3, quads = (d1 + 3) >> 2;
-    const long long total = (long long)runs * quads * d2;
+    const int runs = (d0 + 7) >> 3, rows = (d1 + 15) >> 4;
+    const long long total = (long long)runs * rows * d2;
     for (long long id = blockIdx.x * (long long)blockDim.x + threadIdx.x; id < total;
          id += (long long)gridDim.x * blockDim.x) {
         const int i = (int)(id % runs) * 8;
-        const int j0 = (int)((id / runs) % quads) * 4;
-        const int m = (int)(id / ((long long)runs * quads));
+        const int j0 = (int)((id / runs) % rows) * 16;
+        const int m = (int)(id / ((long long)runs * rows));
         uint32_t bits = 0;
-        for (int l = first; l <= L; ++l) {
+        for (int l = 5; l <= L; ++l) {
             const int e0 = level_dim(n0, l), e1 = level_dim(n1, l);
             const int sh = l - 1;
-            if (node_merged(nodes[off[l] + ((m >> sh) * e1 + (j0 >> sh)) * e0 + (i >> sh)])) bits |= 1u << l;
+            if (node_merged(nodes[off[l] + ((m >> sh) * e1 + (j0 >> sh)) * e0 + (i >> sh)]))
+                bits |= kNested ? (2u << l) - 2u : 1u << l;
+            else if (kNested)
+                break;
         }
         if (!bits) continue;
-        const int nj = min(4, d1 - j0);
+        const int nj = min(16, d1 - j0);
+        uint16_t *const base = mask + ((size_t)m * d1 + j0) * d0 + i;
         if ((d0 & 7) == 0) {
             // 8 masks a row, 16-byte aligned
             const uint32_t b2 = bits | (bits << 16);
-            uint4 w[4];
+            for (int r0 = 0; r0 < nj; r0 += 4) {
+                uint4 w[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (r < nj) w[r] = *reinterpret_cast<const uint4 *>(mask + ((size_t)m * d1 + j0 + r) * d0 + i);
+                for (int r = 0; r < 4; ++r) {
+                    w[r] = make_uint4(b2, b2, b2, b2);
+                    if (!kNested && r0 + r < nj) {
+                        const uint4 o = *reinterpret_cast<const uint4 *>(base + (size_t)(r0 + r) * d0);
+                        w[r] = make_uint4(o.x | b2, o.y | b2, o.z | b2, o.w | b2);
+                    }
+                }
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                if (r >= nj) break;
-                w[r].x |= b2;
-                w[r].y |= b2;
-                w[r].z |= b2;
-                w[r].w |= b2;
-                *reinterpret_cast<uint4 *>(mask + ((size_t)m * d1 + j0 + r) * d0 + i) = w[r];
+                for (int r = 0; r < 4; ++r)
+                    if (r0 + r < nj) *reinterpret_cast<uint4 *>(base + (size_t)(r0 + r) * d0) = w[r];
             }
         } else {
             for (int r = 0; r < nj; ++r) {
-                uint16_t *row = mask + ((size_t)m * d1 + j0 + r) * d0;
-                for (int e = 0; e < 8 && i + e < d0; ++e) row[i + e] = (uint16_t)(row[i + e] | bits);
+                uint16_t *row = base + (size_t)r * d0;
+                for (int e = 0; e < 8 && i + e < d0; ++e) row[e] = (uint16_t)(kNested ? bits : row[e] | bits);
             }
         }
     }
@@ -336,8 +389,10 @@ static int blocks_for(long long n, int block, int cap = 65536)
     return (int)std::max<long long>(1, std::min<long long>(b, cap));
 }
 
-hipError_t launch_build(const nc_ctx *ctx, nc_grid *g, const float *d_kc, unsigned int *d_bad, int *d_zc)
+hipError_t launch_build(const nc_ctx *ctx, nc_grid *g, const float *d_kc, unsigned long long *flags, unsigned int *bad_out)
 {
+    unsigned int *const d_bad = reinterpret_cast<unsigned int *>(flags), *const done = d_bad + 1;
+    int *const d_zc = reinterpret_cast<int *>(flags + 1);
     const int block = 256;
     LayerRule lr{nullptr, g->params.flat_level};
     if (g->params.criterion == 3) {
@@ -348,16 +403,16 @@ hipError_t launch_build(const nc_ctx *ctx, nc_grid *g, const float *d_kc, unsign
         lr.zc = d_zc;
     }
     if (g->L < 1) return hipSuccess;
+    launch_zero_u64(ctx, flags, 1);
     // merge settings per level: the flat grid merges whole levels, as
     // criterion 0 against +inf (always true for finite k) or 0 (never true)
-    auto rule = [&](int l, double &dz_node, double &tau, int &crit) {
-        const bool flat = g->params.criterion == 2;
-        dz_node = g->h[2] * (double)(1 << l);
-        tau = flat ? (l <= g->params.flat_level ? INFINITY : 0.0) : g->params.tau_tilde;
-        crit = flat ? 0 : g->params.criterion;
-    };
+    const bool flat = g->params.criterion == 2;
     LevelRules R{};
-    for (int l = 1; l <= 4; ++l) rule(l, R.dz_node[l], R.tau[l], R.crit[l]);
+    R.crit = flat ? 0 : g->params.criterion;
+    for (int l = 1; l <= g->L; ++l) {
+        R.dz_node[l] = g->h[2] * (double)(1 << l);
+        R.tau[l] = flat ? (l <= g->params.flat_level ? INFINITY : 0.0) : g->params.tau_tilde;
+    }
     const int n0 = g->n[0], n1 = g->n[1], n2 = g->n[2];
     const dim3 fgrid((level_dim(n0, 4) + kBuildWaves - 1) / kBuildWaves, level_dim(n1, 4), level_dim(n2, 4));
     const int lvl = std::min(g->L, 4);
@@ -370,24 +425,17 @@ hipError_t launch_build(const nc_ctx *ctx, nc_grid *g, const float *d_kc, unsign
                            g->off[1], o2, o3, o4, g->d_mask, g->L, g->params.k_gas, R, lr, d_bad);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // the levels above: one launch each from the level below (small)
-    for (int l = 5; l <= g->L; ++l) {
-        const int d0 = level_dim(n0, l), d1 = level_dim(n1, l), d2 = level_dim(n2, l);
-        const int c0 = level_dim(n0, l - 1), c1 = level_dim(n1, l - 1), c2 = level_dim(n2, l - 1);
-        double dz_node = 0.0, tau = 0.0;
-        int crit = 0;
-        rule(l, dz_node, tau, crit);
-        hipLaunchKernelGGL(build_level_kernel, dim3(blocks_for((long long)d0 * d1 * d2, block)), dim3(block), 0,
-                           ctx->stream, (const float2 *)(g->d_nodes + g->off[l - 1]), c0, c1, c2,
-                           g->d_nodes + g->off[l], d0, d1, d2, g->params.k_gas, dz_node, tau, crit, lr, l, n2);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
+    hipLaunchKernelGGL(build_upper_kernel, dim3(level_dim(n0, 8), level_dim(n1, 8), level_dim(n2, 8)), dim3(256), 0,
+                       ctx->stream, g->d_nodes, (const int *)g->d_off, n0, n1, n2, g->L, g->params.k_gas, R, lr,
+                       (const unsigned int *)d_bad, bad_out, done);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
     if (g->L >= 5) {
         const long long runs =
-            (long long)((level_dim(n0, 1) + 7) / 8) * ((level_dim(n1, 1) + 3) / 4) * level_dim(n2, 1);
-        hipLaunchKernelGGL(mask_upper_kernel, dim3(blocks_for(runs, block)), dim3(block), 0, ctx->stream,
-                           (const float2 *)g->d_nodes, (const int *)g->d_off, n0, n1, n2, g->L, 5, g->d_mask);
+            (long long)((level_dim(n0, 1) + 7) / 8) * ((level_dim(n1, 1) + 15) / 16) * level_dim(n2, 1);
+        auto fn = R.crit == 3 ? mask_upper_kernel<false> : mask_upper_kernel<true>;
+        hipLaunchKernelGGL(fn, dim3(blocks_for(runs, block)), dim3(block), 0, ctx->stream, (const float2 *)g->d_nodes,
+                           (const int *)g->d_off, n0, n1, n2, g->L, g->d_mask);
         e = hipGetLastError();
     }
     return e;

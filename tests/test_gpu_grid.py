@@ -174,3 +174,17 @@ def test_invalid_fields():
     with pytest.raises(_lib.NcError) as e:
         api.build_grid(c, device_field(np.ones((4, 4, 4), np.float32)), desc, GridParams(-1.0))
     assert e.value.status == _lib.NC_ERR_RANGE
+
+
+@pytest.mark.parametrize("shape", [(24, 40, 1100), (8, 2050, 16), (513, 3, 18), (300, 17, 261)])
+@pytest.mark.parametrize("crit", [0, 1, 2, 3])
+def test_levels_above_the_fused_pass(shape, crit):
+    """Nodes above level 4 from one workgroup and from many, levels above 8
+    (nx or ny or nz over 256), last nodes in part, large voxels (their bits in the mask)."""
+    rng = np.random.default_rng(sum(shape) + crit)
+    k = (rng.random(shape) ** 8 * 60).astype(np.float32)
+    k[:, :, shape[2] // 3:] = 0.0
+    k[: shape[0] // 2] = 0.0
+    nz, ny, nx = shape
+    for flat in (2, 7):
+        _compare(FieldDesc(nx, ny, nz, 0, 0, 0, 0.05, 0.05, 0.002), k, 0.4 * flat, 0.02, crit, flat)

@@ -156,16 +156,17 @@ __device__ __attribute__((always_inline)) inline void tile_forward(const GuideFr
     }
 }
 
+// four floats at any float's address
+struct __attribute__((packed, aligned(4))) Float4Any {
+    float v[4];
+};
+
 // X: records as rows of `rec_stride` floats, the vertex's 7 values first (the 15
 // network inputs are formed from them); Z: n x 48 raw outputs, fp32.
 // Bound by latency below some 10^4 records and by LDS and matrix core issue above;
 // with a wave per workgroup that fetched its weights from L2 for every tile,
 // 131072 records took 64 us and 10^6 352 us, now 18 and 72 (152 registers: three
 // workgroups a CU).
-struct __attribute__((packed, aligned(4))) Float4Any {
-    float v[4];
-};
-
 __global__ __launch_bounds__(256) void guide_forward_kernel(GuideWeights W, const float *__restrict__ X, int n,
                                                             int rec_stride, float *__restrict__ Z)
 {

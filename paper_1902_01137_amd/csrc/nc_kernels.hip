@@ -2768,6 +2768,10 @@ Shape choose_shape(const nc_ctx *ctx, const nc_grid *g, int block_default, size_
     Shape sh;
     sh.block = ctx->launch.block > 0 ? ctx->launch.block : block_default;
     sh.block = std::max(64, std::min(256, (sh.block / 64) * 64));
+    // a workgroup that reserves LDS holds its own copy of the network (29 KB): with one or
+    // two waves each, too few fit a CU (48 views x 4 suns, 4 spp: 1009 ms at one wave,
+    // 461 ms at four)
+    if (reserve > 0) sh.block = std::max(sh.block, 256);
     const int waves = ctx->launch.waves_per_cu > 0 ? ctx->launch.waves_per_cu : waves_default > 0 ? waves_default : 16;
     sh.wgs = std::max(1, ctx->num_cus * waves / (sh.block / 64));
     // one sample per queue item: the lanes of a wave trace neighbouring pixels

@@ -447,13 +447,13 @@ __global__ __launch_bounds__(256) void flux_tail_kernel(FluxArgs A)
     const HGc &hg = A.op.hg;
     int up = 0, gin = 0, gout = 0, vabs = 0;
     double adj_s = 0.0, adj_g = 0.0, adj_a = 0.0;
-    // the wave's photons: wave, wave + waves, ... one per quad
-    for (unsigned long long first = wave; first < count; first += 16ull * waves) {
-        const unsigned long long i = first + (unsigned long long)quad * waves;
+    // the wave's photons: wave, wave + waves, ...; a quad whose photon has ended takes its next one
+    unsigned long long i = wave + (unsigned long long)quad * waves;
+    {
         QuadRay r;
         RngQuad rng;
         rng.buf = s_rng + (threadIdx.x >> 2) * 16u;
-        int phase = kPhIdle, res = 0, segs = 0;
+        int phase = kPhSample, res = 0, segs = 0;
         uint32_t id0 = 0, id1 = 0;
         bool scattered = false, e_up = false, e_in = false, e_out = false, e_abs = false;
         float sig_s = 0.0f, sig_g = 0.0f, sig_a = 0.0f, tau = 0.0f, kc_hit = 0.0f;
@@ -468,8 +468,26 @@ __global__ __launch_bounds__(256) void flux_tail_kernel(FluxArgs A)
             r.enter(G);
             phase = ((r.khat > 0.0f) & (tau < r.khat * (r.texit - r.t))) ? kPhCollide : kPhCross;
         };
-        if (i < count) {
+        auto ray_start = [&](float dir) __attribute__((always_inline)) {
+            const bool hit = r.setup(G, dir);
+            tau = neg_log_unit(1.0f - u01());
+            if (hit) {
+                r.first_voxel(A.g, G, ns, A.op.mscale);
+                enter();
+            } else {
+                // misses the box: the next step finds the ray outside
+                r.t = r.tend = r.texit = 0.0f;
+                r.khat = 0.0f;
+                r.kmin = 0.0f;
+                r.lev = 0;
+                phase = kPhCross;
+            }
+        };
+        auto take_photon = [&]() __attribute__((always_inline)) {
             const uint32_t *w = A.tail + i;
+            i += 16ull * waves;
+            r.vc = -1;
+            r.vlev = 0;
             const size_t cap = A.tail_cap;
             auto get_u = [&](int k) { return w[(size_t)k * cap]; };
             auto get_f = [&](int k) { return __uint_as_float(w[(size_t)k * cap]); };
@@ -510,24 +528,21 @@ __global__ __launch_bounds__(256) void flux_tail_kernel(FluxArgs A)
                 if ((fl >> (8 + ax)) & 1) r.c -= r.d > 0.0f ? 1 : -1;
                 r.faces(G);
             }
-        }
-        auto ray_start = [&](float dir) __attribute__((always_inline)) {
-            const bool hit = r.setup(G, dir);
-            tau = neg_log_unit(1.0f - u01());
-            if (hit) {
-                r.first_voxel(A.g, G, ns, A.op.mscale);
-                enter();
-            } else {
-                // misses the box: the next step finds the ray outside
-                r.t = r.tend = r.texit = 0.0f;
-                r.khat = 0.0f;
-                r.kmin = 0.0f;
-                r.lev = 0;
-                phase = kPhCross;
-            }
         };
         // (one loop, in which every photon of the wave takes its next step)
-        while (__ballot(phase < kPhSample)) {
+        for (;;) {
+            if (phase == kPhSample) {
+                if (first_lane) {
+                    up += e_up;
+                    gin += e_in;
+                    gout += e_out;
+                    vabs += e_abs;
+                }
+                e_up = e_in = e_out = e_abs = false;
+                phase = kPhIdle;
+                if (i < count) take_photon();
+            }
+            if (!__ballot(phase < kPhSample)) break;
             if (phase == kPhEvent) {
                 phase = kPhSample;
                 if (res == kReal) {
@@ -608,11 +623,14 @@ __global__ __launch_bounds__(256) void flux_tail_kernel(FluxArgs A)
                 }
             }
         }
-        if (!kAdjoint) {
-            up += lane_count(e_up & first_lane);
-            gin += lane_count(e_in & first_lane);
-            gout += lane_count(e_out & first_lane);
-            vabs += lane_count(e_abs & first_lane);
+    }
+    if (!kAdjoint) {
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            up += __shfl_xor(up, off);
+            gin += __shfl_xor(gin, off);
+            gout += __shfl_xor(gout, off);
+            vabs += __shfl_xor(vabs, off);
         }
     }
     flux_totals<kAdjoint>(A, up, gin, gout, vabs, adj_s, adj_g, adj_a);
@@ -664,9 +682,9 @@ hipError_t launch_flux(const nc_ctx *ctx, const nc_grid *g, const float *d_kc, c
         A.span = (n_photons + 8 * kChunk - 1) / (8 * kChunk) * kChunk;
     }
     // the last photons (not where statistics are kept or on a grid too large for the tail kernel's arithmetic)
-    A.tail_lanes = n_photons <= 2ull * wgs * 256 ? 2 * kTailLanes : kTailLanes;
-    const long long tail_paths = (long long)wgs * 4 * A.tail_lanes;   // at most
-    A.tail = !counters && A.g.narrow && tail_paths <= (long long)kTailCap
+    const TailShape ts = tail_shape(n_photons, (long long)wgs * 4, kTailPhotons);
+    A.tail_lanes = ts.lanes;
+    A.tail = !counters && A.g.narrow && ts.lanes > 0
                  ? reinterpret_cast<uint32_t *>(ctx->d_scratch + kScratchWords)
                  : nullptr;
     A.tail_count = reinterpret_cast<unsigned int *>(heads + 8);   // in the first queue head's line, zeroed with it
@@ -675,9 +693,8 @@ hipError_t launch_flux(const nc_ctx *ctx, const nc_grid *g, const float *d_kc, c
     void *args[] = {&A};
     const hipError_t e = hipLaunchKernel(fn, dim3(wgs), dim3(256), args, lds, ctx->stream);
     if (e != hipSuccess || !A.tail) return e;
-    const int tail_waves = (int)std::min<long long>(tail_paths, kTailWaves);
     return hipLaunchKernel(grad ? (const void *)flux_tail_kernel<true> : (const void *)flux_tail_kernel<false>,
-                           dim3((tail_waves + 3) / 4), dim3(256), args, node_bytes, ctx->stream);
+                           dim3((ts.waves + 3) / 4), dim3(256), args, node_bytes, ctx->stream);
 }
 
 }  // namespace nc

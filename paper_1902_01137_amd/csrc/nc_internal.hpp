@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <string>
 
 #include "nc_device.hpp"
@@ -173,17 +174,30 @@ hipError_t launch_philox(const nc_ctx *ctx, const uint32_t *ctr, const uint32_t 
 // launch).  Either the context's buffers or the no-allocation scratch.
 constexpr size_t kRareBytes = 1536;
 // The tail kernels (the last paths of a render call, the last photons of a flux
-// call): a wave hands its paths over when kTailLanes or fewer are left (twice as
-// many in a launch of hardly more than one path a lane), so a launch of 8192
-// waves (32 per CU) hands over kTailCap at most, each as kTailWords words at most
-// (42 MB per context).  kTailWaves waves (5 per SIMD, what the kernels' registers
-// allow) share them, 16 at a time.  Measured (505 k paths, ragged field / 65 k,
-// blob / 67 M, cumulus step, ms): 16 lanes 7.2 / 0.82 / 25.1, 32 lanes 7.4 and 6.3
-// (two clouds) / 0.69 / 26.0, 8 lanes 8.1 / 0.94 / 25.4.
-constexpr int kTailLanes = 16;
-constexpr uint32_t kTailCap = 8192 * 2 * kTailLanes;
-constexpr int kTailWords = 40;
-constexpr int kTailWaves = 5120;
+// call): once its queue is drained a wave hands its paths over when no more than
+// these are left: all of them in a launch of hardly more than a path a lane, which is all
+// tail (ms at 64 / 32 / 16 lanes: 65 k paths over a blob 0.60 / 0.70 / 0.84, 505 k over
+// a ragged field 6.1 / 6.7 / 7.1, 200 k photons 5.1 / 5.3 / 5.4), else 32 paths (solar disc
+// view of 8.4 M 37.1 / 35.6 / 37.1, cumulus step of 67 M 49.7 / 49.2 / 49.3, means of three
+// clouds) or 16 photons (10^7: 11.1 / 10.3 / 9.7).  The context holds kTailCap of them (58 MB), 64 of
+// each of 6144 waves; launches of more waves hand over fewer of each.  Sixteen at a
+// time, kTailWaves waves share them, in large launches (fewer, longer lists) kTailWavesLarge.
+constexpr uint32_t kTailCap = 6144 * 64;
+constexpr int kTailWords = 37;
+constexpr int kTailWaves = 5120, kTailWavesLarge = 4096;
+constexpr int kTailPaths = 32, kTailPhotons = 16;
+struct TailShape {
+    int lanes;        // paths of a wave at which it hands them over (0: never)
+    int waves;        // of the tail kernel
+};
+inline TailShape tail_shape(unsigned long long items, long long waves, int lanes)
+{
+    const bool small = items <= 128ull * (unsigned long long)waves;
+    TailShape t;
+    t.lanes = (int)std::min<long long>(small ? 64 : lanes, (long long)kTailCap / waves);
+    t.waves = (int)std::min<long long>(waves * t.lanes, small ? kTailWaves : kTailWavesLarge);
+    return t;
+}
 struct RenderScratch {
     JobView *jobs;
     unsigned long long *rare;

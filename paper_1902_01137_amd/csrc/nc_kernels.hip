@@ -879,6 +879,7 @@ struct RenderArgs {
     int lds_first, lds_nodes;
 };
 
+constexpr int kAllPhases = 16;      // guided paths left in a wave at which it runs all phases in each trip
 constexpr int kGuideMaxWait = 8;   // trips a partial tile of guided lanes may wait for more
 enum RenderMode { kPlain = 0, kGuided = 1, kCollect = 2 };
 // ratio estimators: Russian roulette of a sun ray's estimate below this
@@ -1830,7 +1831,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
         }
         // a guided wave with few paths runs every phase in one trip instead, in the
         // order a path goes through them: each lane then advances at every trip
-        const bool all = kMode == kGuided && queue_done && n_other + n_guide <= kTailLanes;
+        const bool all = kMode == kGuided && queue_done && n_other + n_guide <= kAllPhases;
         const bool run_step = all || run == kPhCross, run_coll = all || run == kPhCollide;
         const bool run_event = all || run == kPhEvent, run_sample = run == kPhSample || (all && n_sample > 0);
         const bool run_guide = run == kPhGuide;
@@ -2138,7 +2139,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kWavesPerEU
 // paths at most and the network's registers left 3 waves a SIMD: 15.0 ms against
 // 14.0 at the cumulus view of 512^2 pixels, 32 samples.)
 // Measured against the main kernel running all phases in one trip below 16 paths
-// (ms): 505 k paths over a ragged field 12.2 -> 7.3, 65 k over a blob 0.99 -> 0.68,
+// (ms): 505 k paths over a ragged field 12.2 -> 6.1, 65 k over a blob 0.99 -> 0.60,
 // 6.3 M of a batch of 48 views 35.8 -> 31, 67 M over a cumulus field 26.2 -> 23.1.
 // A lone wave issues an instruction every 7 to 8 cycles whatever its kind, so what
 // is left is the count of instructions on the way from one scattering to the next.
@@ -2166,13 +2167,14 @@ __global__ __launch_bounds__(256) void render_tail_kernel(RenderArgs A)
     constexpr int kEventDraws = 3;
     auto on_axis = [&](const float v[3]) { return quad_pick(ax, v[0], v[1], v[2]); };
     const float gpos = quad_pick(ax, A.gpos[0], A.gpos[1], A.gpos[2]);
-    // the wave's paths: wave, wave + waves, ... one per quad
-    for (unsigned long long first = wave; first < count; first += 16ull * waves) {
-        const unsigned long long i = first + (unsigned long long)quad * waves;
+    // the wave's paths: wave, wave + waves, ...; a quad whose path has ended takes its next one
+    unsigned long long i = wave + (unsigned long long)quad * waves;
+    bool have = false;
+    {
         QuadRay r;
         RngQuad rng;
         rng.buf = s_rng + (threadIdx.x >> 2) * 16u;
-        int phase = kPhIdle, job = 0, pix = 0, s = 0, order = 0, segs = 0, res = 0;
+        int phase = kPhSample, job = 0, pix = 0, s = 0, order = 0, segs = 0, res = 0;
         bool shadow = false, ground_ev = false, start = false;
         float acc = 0.0f, acc2 = 0.0f, Lp = 0.0f, tau = 0.0f, kc_hit = 0.0f, w_nee = 0.0f, p_cont = 0.0f;
         float beta = 1.0f, kev = 0.0f, kg = A.g.k_gas, pd = 0.0f, sun = 0.0f;
@@ -2189,59 +2191,6 @@ __global__ __launch_bounds__(256) void render_tail_kernel(RenderArgs A)
             if (kSun == 2 && shadow) r.khat = fmaxf(r.khat - (r.kmin + path_kg()), 0.0f);
             phase = ((r.khat > 0.0f) & (tau < r.khat * (r.texit - r.t))) ? kPhCollide : kPhCross;
         };
-        if (i < count) {
-            const uint32_t *w = A.tail + i;
-            const size_t cap = A.tail_cap;
-            auto get_i = [&](int k) { return (int)w[(size_t)k * cap]; };
-            auto get_f = [&](int k) { return __uint_as_float(w[(size_t)k * cap]); };
-            const int fl = get_i(kTwFlags);
-            phase = fl & 7;
-            shadow = (fl & 8) != 0;
-            ground_ev = (fl & 16) != 0;
-            res = (fl >> 5) & 3;
-            r.lev = (fl >> 12) & 0xff;
-            job = get_i(kTwInts);
-            pix = get_i(kTwInts + 1);
-            s = get_i(kTwInts + 2);
-            order = get_i(kTwInts + 3);
-            segs = get_i(kTwInts + 4);
-            acc = get_f(kTwFloats);
-            acc2 = get_f(kTwFloats + 1);
-            Lp = get_f(kTwFloats + 2);
-            tau = get_f(kTwFloats + 3);
-            kc_hit = get_f(kTwFloats + 4);
-            w_nee = get_f(kTwFloats + 5);
-            p_cont = get_f(kTwFloats + 6);
-            r.t = get_f(kTwFloats + 7);
-            r.tend = get_f(kTwFloats + 8);
-            r.texit = get_f(kTwFloats + 9);
-            r.khat = get_f(kTwFloats + 10);
-            r.kmin = get_f(kTwFloats + 11);
-            beta = get_f(kTwFloats + 12);   // (an irradiance sensor's paths have a weight too)
-            if (kMode == kCollect) kev = get_f(kTwFloats + 13);
-            if (kExt) kg = get_f(kTwFloats + 14);
-            r.o = get_f(kTwAxes + 5 * ax);
-            r.d = get_f(kTwAxes + 5 * ax + 1);
-            pd = get_f(kTwAxes + 5 * ax + 2);
-            sun = get_f(kTwAxes + 5 * ax + 3);
-            r.c = get_i(kTwAxes + 5 * ax + 4);
-            {
-                const float d3[3] = {r.d, r.d, r.d};
-                float inv3[3];
-                ray_inverse(d3, inv3);
-                r.inv = inv3[0];
-            }
-            rng.resume((uint32_t)get_i(kTwDraw), fl >> 20, (uint32_t)pix, A.sample_base + (uint32_t)s,
-                       A.stream_base + (uint32_t)job, A.key0, A.key1);
-            if (phase == kPhRay) {
-                r.locate(A.g, G, ns, A.op.mscale);
-                enter();
-            } else {
-                // a cell of the current voxel from the one past it
-                if ((fl >> (8 + ax)) & 1) r.c -= r.d > 0.0f ? 1 : -1;
-                r.faces(G);
-            }
-        }
         // across the exit face into the next voxel, or the ray's end
         auto cross = [&]() __attribute__((always_inline)) {
             const float dt = r.texit - r.t;
@@ -2421,7 +2370,80 @@ __global__ __launch_bounds__(256) void render_tail_kernel(RenderArgs A)
                 phase = kPhCross;
             }
         };
-        while (__ballot(phase < kPhSample)) {
+        auto take_path = [&]() __attribute__((always_inline)) {
+            const uint32_t *w = A.tail + i;
+            i += 16ull * waves;
+            r.vc = -1;
+            r.vlev = 0;
+            const size_t cap = A.tail_cap;
+            auto get_i = [&](int k) { return (int)w[(size_t)k * cap]; };
+            auto get_f = [&](int k) { return __uint_as_float(w[(size_t)k * cap]); };
+            const int fl = get_i(kTwFlags);
+            phase = fl & 7;
+            shadow = (fl & 8) != 0;
+            ground_ev = (fl & 16) != 0;
+            res = (fl >> 5) & 3;
+            r.lev = (fl >> 12) & 0xff;
+            job = get_i(kTwInts);
+            pix = get_i(kTwInts + 1);
+            s = get_i(kTwInts + 2);
+            order = get_i(kTwInts + 3);
+            segs = get_i(kTwInts + 4);
+            acc = get_f(kTwFloats);
+            acc2 = get_f(kTwFloats + 1);
+            Lp = get_f(kTwFloats + 2);
+            tau = get_f(kTwFloats + 3);
+            kc_hit = get_f(kTwFloats + 4);
+            w_nee = get_f(kTwFloats + 5);
+            p_cont = get_f(kTwFloats + 6);
+            r.t = get_f(kTwFloats + 7);
+            r.tend = get_f(kTwFloats + 8);
+            r.texit = get_f(kTwFloats + 9);
+            r.khat = get_f(kTwFloats + 10);
+            r.kmin = get_f(kTwFloats + 11);
+            beta = get_f(kTwFloats + 12);   // (an irradiance sensor's paths have a weight too)
+            if (kMode == kCollect) kev = get_f(kTwFloats + 13);
+            if (kExt) kg = get_f(kTwFloats + 14);
+            r.o = get_f(kTwAxes + 5 * ax);
+            r.d = get_f(kTwAxes + 5 * ax + 1);
+            pd = get_f(kTwAxes + 5 * ax + 2);
+            sun = get_f(kTwAxes + 5 * ax + 3);
+            r.c = get_i(kTwAxes + 5 * ax + 4);
+            {
+                const float d3[3] = {r.d, r.d, r.d};
+                float inv3[3];
+                ray_inverse(d3, inv3);
+                r.inv = inv3[0];
+            }
+            rng.resume((uint32_t)get_i(kTwDraw), fl >> 20, (uint32_t)pix, A.sample_base + (uint32_t)s,
+                       A.stream_base + (uint32_t)job, A.key0, A.key1);
+            if (phase == kPhRay) {
+                r.locate(A.g, G, ns, A.op.mscale);
+                enter();
+            } else {
+                // a cell of the current voxel from the one past it
+                if ((fl >> (8 + ax)) & 1) r.c -= r.d > 0.0f ? 1 : -1;
+                r.faces(G);
+            }
+        };
+        for (;;) {
+            if (phase == kPhSample) {
+                if (have && G.ql == 0) {
+                    // the path's end, as the renderer's sample phase adds it
+                    const JobView &J = jobs[job];
+                    if (kMode == kCollect) A.col.final_L[(size_t)pix * A.col_spp + s] = Lp;
+                    acc += Lp;
+                    acc2 += Lp * Lp;
+                    const unsigned long long q = J.out_off + (unsigned long long)pix;
+                    const double S = (double)J.S;
+                    unsafeAtomicAdd(lds_get(s_rare.sum) + q, S * (double)acc);
+                    unsafeAtomicAdd(lds_get(s_rare.sumsq) + q, S * S * (double)acc2);
+                }
+                have = i < count;
+                phase = kPhIdle;
+                if (have) take_path();
+            }
+            if (!__ballot(phase < kPhSample)) break;
             // (one loop, in which every path of the wave takes its next step: with a
             // loop over each ray's voxels inside, a path in a dense cloud would
             // wait at every ray for the wave's longest)
@@ -2432,17 +2454,6 @@ __global__ __launch_bounds__(256) void render_tail_kernel(RenderArgs A)
             }
             if (phase == kPhCross) cross();
             if (phase == kPhCollide) collide();
-        }
-        if (phase == kPhSample && G.ql == 0) {
-            // the path's end, as the renderer's sample phase adds it
-            const JobView &J = jobs[job];
-            if (kMode == kCollect) A.col.final_L[(size_t)pix * A.col_spp + s] = Lp;
-            acc += Lp;
-            acc2 += Lp * Lp;
-            const unsigned long long q = J.out_off + (unsigned long long)pix;
-            const double S = (double)J.S;
-            unsafeAtomicAdd(lds_get(s_rare.sum) + q, S * (double)acc);
-            unsafeAtomicAdd(lds_get(s_rare.sumsq) + q, S * S * (double)acc2);
         }
     }
 }
@@ -2658,15 +2669,13 @@ hipError_t launch_render(const nc_ctx *ctx, const nc_grid *g, const float *d_kc,
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(zero_u64_kernel, dim3(2 * n_sets), dim3(64), 0, ctx->stream, scr.queue, 128 * n_sets);
     if (collect) hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, ctx->stream, collect->count, 1);
-    // (a launch of hardly more than a path per lane is all tail: earlier there)
-    A.tail_lanes = items <= 2ull * wgs * sh.block ? 2 * kTailLanes : kTailLanes;
-    const long long tail_paths = (long long)wgs * (sh.block / 64) * A.tail_lanes;   // at most
-    if (tail_paths > (long long)kTailCap) A.tail = nullptr;
+    const TailShape ts = tail_shape(items, (long long)wgs * (sh.block / 64), kTailPaths);
+    A.tail_lanes = ts.lanes;
+    if (ts.lanes == 0) A.tail = nullptr;
     void *args[] = {&A};
     e = hipLaunchKernel(fn, dim3(wgs), dim3(sh.block), args, lds, ctx->stream);
     if (e != hipSuccess || !A.tail) return e;
-    const int tail_waves = (int)std::min<long long>(tail_paths, kTailWaves);
-    return hipLaunchKernel(tail_kernel(mode, est, ext), dim3((tail_waves + 3) / 4), dim3(256), args, node_bytes,
+    return hipLaunchKernel(tail_kernel(mode, est, ext), dim3((ts.waves + 3) / 4), dim3(256), args, node_bytes,
                            ctx->stream);
 }
 

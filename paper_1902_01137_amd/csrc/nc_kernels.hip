@@ -2507,10 +2507,10 @@ hipError_t launch_render(const nc_ctx *ctx, const nc_grid *g, const float *d_kc,
                          const CollectView *collect)
 {
     const int mode = guides ? kGuided : collect ? kCollect : kPlain;
-    const int block0 = ctx->launch.block > 0 ? std::max(64, std::min(256, (ctx->launch.block / 64) * 64)) : 256;
     const bool ext = op.kd_n > 0 || op.tab.n > 0 || op.cone;   // the extended medium: its own kernel variants
-    const size_t guide_bytes =
-        mode == kGuided ? (size_t)kGuideWeightBytes + (size_t)(block0 / 64) * kGuideScratchPerWave : 0;
+    // (the network's copy and a scratch tile for each of the four waves: choose_shape gives
+    // a workgroup that reserves LDS four waves)
+    const size_t guide_bytes = mode == kGuided ? (size_t)kGuideWeightBytes + 4 * (size_t)kGuideScratchPerWave : 0;
     Shape sh = choose_shape(ctx, g, 256, guide_bytes, 0);
     RenderRare rare;
     rare.seed = s.seed;

@@ -172,3 +172,31 @@ def test_trained_guide_lowers_variance():
     ratio = float((gse ** 2).sum() / (pse ** 2).sum())
     print("variance ratio guided/plain = %.3f" % ratio)
     assert ratio < 0.9, ratio
+
+
+@pytest.mark.parametrize("block", [64, 128])
+@pytest.mark.parametrize("batch", [False, True], ids=["view", "batch"])
+def test_guided_launch_settings_keep_the_image(block, batch):
+    """A guided workgroup has four waves whatever the setting, each with its tile of scratch beside the network."""
+    sc = inputs.scene_small()
+    c = ctx()
+    kd = device_field(sc.kc)
+    g = api.build_grid(c, kd, sc.desc, sc.grid)
+    guides = [api.Guide(c, seed=s) for s in (9, 10)]
+    smp = Sampling(seed=17, spp=24, guide_frac=0.5)
+
+    def image():
+        if batch:
+            return api.render_batch(c, g, kd, [(sc.camera, sc.optics)] * 2, smp, guide=guides)[:2]
+        return api.render_guided(c, g, kd, sc.optics, sc.camera, smp, guides[0])
+
+    c.set_launch()
+    ref = image()
+    try:
+        c.set_launch(block=block)
+        out = image()
+    finally:
+        c.set_launch()
+    for a, b in zip(out, ref):
+        assert bool(torch.isfinite(a).all()) and float(b.sum()) > 0.0
+        torch.testing.assert_close(a, b, rtol=1e-12, atol=1e-12)
